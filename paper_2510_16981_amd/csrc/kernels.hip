@@ -1028,9 +1028,16 @@ __device__ __forceinline__ uint32_t lds_addr(const unsigned char* p) {
 //     issued between two MFMAs of the previous step;
 //   * the barrier that publishes the next slice sits right after the first
 //     MFMA of the current slice's second step (that MFMA keeps running);
-//   * right after it, the copy that refills the slot just consumed and the
-//     reads of the next slice's first step are spread over the remaining
-//     MFMAs.
+//   * right after it, the reads of the next slice's first step and the copies
+//     that refill the slot just consumed are spread over the remaining
+//     MFMAs; with 8 waves half of the copies wait for the next slice's first
+//     step.  (All behind one barrier they are 32 KB asked for in the time of
+//     three MFMAs, more than the CU's copy path of 64 B/clk takes, and a wave
+//     that cannot issue its copy issues no MFMA either.  48 units of 1792 x
+//     4096: Gram 674 -> 659 us, a symmetric S x S x S product 377 -> 358, the
+//     apply 1200 -> 1177; two layers of the 8B-shaped model's block step
+//     10.49 -> 10.16 ms.  The 4-wave kernels of 128 x 128 tiles got 1-2%
+//     slower with it, so they keep one burst.)
 //
 // Slices past K are copied too (as zeros, through an out-of-range offset),
 // so the loop has no branches and every wait is a constant count.
@@ -1292,12 +1299,17 @@ __global__ __launch_bounds__(64 * WM * WN) void k_ns_gemm_dmap(const GemmDesc* _
     constexpr bool MATH = decltype(math)::value;
     // Copies per wave and slice: all LPW, or the X copies alone.
     constexpr int LP = decltype(sh)::value ? XG / W : LPW;
-    // Prologue: fill the ring, publish slice kb, read its first K step.
+    // Of the refill that follows slice kt's barrier, LP - LB copies go into
+    // the rest of its step 1 and LB into step 0 of slice kt + 1.
+    constexpr int LB = W == 8 ? LP / 2 : 0;
+    // Prologue: fill the ring (its last LB copies are issued by the first
+    // step 0), publish slice kb, read its first K step.
 #pragma unroll
     for (int s = 0; s < NS; ++s)
 #pragma unroll
-      for (int jj = 0; jj < LP; ++jj) copy(kb + s, jj);
-    __builtin_amdgcn_s_waitcnt(vmcnt_imm((NS - 1) * LP));
+      for (int jj = 0; jj < LP; ++jj)
+        if (s < NS - 1 || jj < LP - LB) copy(kb + s, jj);
+    __builtin_amdgcn_s_waitcnt(vmcnt_imm((NS - 1) * LP - LB));
     barrier_no_fence();
     if constexpr (MATH)
 #pragma unroll
@@ -1315,7 +1327,8 @@ __global__ __launch_bounds__(64 * WM * WN) void k_ns_gemm_dmap(const GemmDesc* _
         else
           __builtin_amdgcn_s_setprio(0);
       }
-      // Step 0 of slice kt, with the reads of its step 1.
+      // Step 0 of slice kt, with the reads of its step 1 and the rest of the
+      // refill of slice kt - 1's slot.
 #pragma unroll
       for (int q = 0; q < NM; ++q) {
         if constexpr (MATH) {
@@ -1323,6 +1336,8 @@ __global__ __launch_bounds__(64 * WM * WN) void k_ns_gemm_dmap(const GemmDesc* _
 #pragma unroll
           for (int o = q * RPM; o < (q + 1) * RPM && o < NR; ++o) read_op(sh, f1, y1l, y1h, kt, 1, o);
         }
+#pragma unroll
+        for (int o = q * LB / NM; o < (q + 1) * LB / NM; ++o) copy(kt + NS - 1, LP - LB + o);
         __builtin_amdgcn_sched_barrier(0);
       }
       frag_wait(f1, y1l, y1h);
@@ -1337,8 +1352,9 @@ __global__ __launch_bounds__(64 * WM * WN) void k_ns_gemm_dmap(const GemmDesc* _
       // wave reads slice kt any more, so its slot takes slice kt + NS.
       __builtin_amdgcn_s_waitcnt(vmcnt_imm(2 * LP));
       barrier_no_fence();
-      // Step 1, rest, with the reads of slice kt + 1 and the refill copies.
-      constexpr int OPS = LP + NR;
+      // Step 1, rest, with the reads of slice kt + 1 and the refill's first
+      // LP - LB copies.
+      constexpr int OPS = LP - LB + NR;
 #pragma unroll
       for (int q = H; q < NM; ++q) {
         if constexpr (MATH) mfma(f1, q);
