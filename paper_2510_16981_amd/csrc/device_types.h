@@ -75,7 +75,8 @@ struct GemmDesc {
 
 // Workgroup tile shapes of the NS GEMM (rows x columns of C per workgroup):
 // register-staged K loop (any dtype, any K) or LDS-DMA K loop (bf16, K a
-// multiple of 8).
+// multiple of 8; kGemmWaveK64: every wave of a workgroup runs a quarter of
+// the tile's K slices).
 // kGemm128x128Split2 runs two K halves of each tile in one 8-wave
 // workgroup.  kGemmDma128x128 .. kGemmDma256x256 are kept as numbers only:
 // the planner turns them into the interleaved kernels of the same shapes.
@@ -86,16 +87,20 @@ enum GemmVariant : int32_t {
   kGemmDmaP128x128 = 7, kGemmDmaP256x128 = 8, kGemmDmaP256x256 = 9,
   kGemmDmaP192x256 = 10, kGemmDmaP256x192 = 11, kGemmDmaP192x192 = 12,
   kGemmDmaP256x256W8 = 13, kGemmDmaP192x256W8 = 14, kGemmDmaP256x192W8 = 15,
-  kNumGemmVariants = 16
+  kNumGemmVariants = 16,  // the variants muonbp_options.tile_policy can name
+  kGemmWaveK64 = 16,      // chosen by the planner only
+  kNumGemmKernels = 17
 };
-constexpr int kGemmTileRows[kNumGemmVariants] = {128, 256, 256, 128, 256, 256, 128, 128,
-                                                 256, 256, 192, 256, 192, 256, 192, 256};
-constexpr int kGemmTileCols[kNumGemmVariants] = {128, 128, 256, 128, 128, 256, 128, 128,
-                                                 128, 256, 256, 192, 192, 256, 256, 192};
-constexpr bool kGemmIsDma[kNumGemmVariants] = {false, false, false, true, true, true, false, true,
-                                               true,  true,  true,  true, true, true, true,  true};
+constexpr int kGemmTileRows[kNumGemmKernels] = {128, 256, 256, 128, 256, 256, 128, 128, 256,
+                                                256, 192, 256, 192, 256, 192, 256, 64};
+constexpr int kGemmTileCols[kNumGemmKernels] = {128, 128, 256, 128, 128, 256, 128, 128, 128,
+                                                256, 256, 192, 192, 256, 256, 192, 64};
+constexpr bool kGemmIsDma[kNumGemmKernels] = {false, false, false, true, true, true, false, true, true,
+                                              true,  true,  true,  true, true, true, true,  true};
 // Interleaved DMA kernels (k_ns_gemm_dmap).
-constexpr bool gemm_is_dmap(int v) { return v >= kGemmDmaP128x128; }
+constexpr bool gemm_is_dmap(int v) { return v >= kGemmDmaP128x128 && v <= kGemmDmaP256x192W8; }
+// Kernels whose apply can read Z row-major.
+constexpr bool gemm_reads_rows(int v) { return gemm_is_dmap(v) || v == kGemmWaveK64; }
 
 // One workgroup tile of a grouped launch: problem index and packed
 // (tile row << 16 | tile column).

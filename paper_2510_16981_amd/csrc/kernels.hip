@@ -1427,6 +1427,265 @@ __global__ __launch_bounds__(64 * WM * WN) void k_ns_gemm_dmap(const GemmDesc* _
                               ti == tj && d.sym && !above, alpha);
 }
 
+// ---------------------------------------------------------------- NS GEMM, K split over the waves of a tile
+//
+// For launches of few tiles (the units of small shards, or a handful of
+// them).  There a 128 x 128 tile leaves most CUs idle and runs at one wave per
+// SIMD, each slice exposing the latency of its LDS reads and its barrier
+// (690 clocks for 256 of MFMA).  Here the tile is 64 x 64 and each of the four
+// waves runs every fourth 32-element K slice of the whole tile through a ring
+// of its own (2 slots of 4 KB X + 4 KB Y, in the layouts of the DMA kernel
+// above), so that the K loop has no barrier and a quarter of the iterations;
+// the four partial sums are then added through LDS in wave order, each wave
+// finishing one 32 x 32 quadrant.  72 KB of LDS: two workgroups per CU.
+// Bound by the fixed cost of a launch up to one tile per CU, by the copies (8
+// KB per tile and slice at 64 B/clk) beyond.  Measured per launch against
+// 128 x 128 tiles, us: 16 units of 128 x 512: 5.7 / 5.4 / 5.0 against 8.2 /
+// 6.6 / 6.2 (Gram, polynomial, apply), two of 304 x 1000: 6.9 / 5.6 / 5.6
+// against 13.0 / 8.5 / 7.8, 12 of 512 x 512: 8.7 / 9.5 against 10.3 / 11.1; a
+// ring of 4 slots (one workgroup per CU) took 5.2-12 on the same launches,
+// and operands loaded straight into registers, whose 16-byte lanes lie on 16
+// rows, 1.4-2 times as long.
+//
+// The arithmetic is the DMA kernels' (alpha sum, + beta D, + gamma on the
+// diagonal, one rounding to bf16) with the sum in four parts.  D, where set,
+// is symmetric.  Chunks of 8 elements that straddle N (or M, in Ct) are
+// stored whole: they end inside the padded row, and what lies past N is zero.
+//
+// Staging of the finished quadrants: 32 rows of Ct (n) of 64 bytes, chunk c
+// at position c ^ swz(n); rows of C are read back with LDS transpose reads.
+template <bool NN>
+__global__ __launch_bounds__(kThreads) void k_ns_gemm_wavek(const GemmDesc* __restrict__ probs,
+                                                            const TileRef* __restrict__ tiles) {
+  constexpr int T = 64, PD = 2, ES = 2, SLOT = 8192;
+  constexpr int kRed = 4 * T * T * 4, kRing = 4 * PD * SLOT;
+  static_assert(kRing <= kRed, "the sums reuse the rings");
+  __shared__ __attribute__((aligned(1024))) unsigned char lds[kRed + 2 * T * T];
+  const TileRef t = tiles[blockIdx.x];
+  const GemmDesc d = probs[t.prob];
+  const float alpha = desc_alpha(d);
+  const int ti = t.ij >> 16, tj = t.ij & 0xffff;
+  const int m0 = ti * T, n0 = tj * T;
+  const int lane = threadIdx.x & 63;
+  const int wave = __builtin_amdgcn_readfirstlane(threadIdx.x >> 6);
+  const int xbytes = d.M * d.ldx * ES, ybytes = (NN ? d.K : d.N) * d.ldy * ES;
+  const __amdgpu_buffer_rsrc_t xr = __builtin_amdgcn_make_buffer_rsrc(const_cast<void*>(d.X), 0, xbytes, kBufferWord3);
+  const __amdgpu_buffer_rsrc_t yr = __builtin_amdgcn_make_buffer_rsrc(const_cast<void*>(d.Y), 0, ybytes, kBufferWord3);
+  // Copies of a slice: 4 x 16 rows of X, then 4 x 16 rows of Y (NN: 4 x 8 k-rows).
+  int xo[4], yo[4], xk[4], yk[4];
+#pragma unroll
+  for (int i = 0; i < 4; ++i) {
+    const int row = 16 * i + (lane >> 2), c = (lane & 3) ^ swz(row);
+    xk[i] = 8 * c;
+    xo[i] = m0 + row < d.M ? ((m0 + row) * d.ldx + 8 * c) * ES : xbytes;
+    if constexpr (NN) {
+      const int kr = 8 * i + (lane >> 3), cn = (lane & 7) ^ (4 * ((kr >> 1) & 1));
+      yk[i] = kr;
+      yo[i] = n0 + 8 * cn < d.N && kr < d.K ? (kr * d.ldy + n0 + 8 * cn) * ES : ybytes;
+    } else {
+      yk[i] = 8 * c;
+      yo[i] = n0 + row < d.N ? ((n0 + row) * d.ldy + 8 * c) * ES : ybytes;
+    }
+  }
+  unsigned char* ring = lds + wave * PD * SLOT;
+  const int nk = (d.K + 31) / 32;
+  const int nit = nk > wave ? (nk - wave + 3) / 4 : 0;  // this wave's slices: wave, wave + 4, ..
+  auto copy = [&](int it) {
+    const int k0 = 32 * (wave + 4 * it);
+    unsigned char* dst = ring + (it % PD) * SLOT;
+#pragma unroll
+    for (int i = 0; i < 4; ++i)
+      dma16(xr, (lds_void_t*)(dst + i * 1024), it < nit && k0 + xk[i] < d.K ? xo[i] : xbytes, k0 * ES);
+#pragma unroll
+    for (int i = 0; i < 4; ++i)
+      dma16(yr, (lds_void_t*)(dst + 4096 + i * 1024), it < nit && k0 + yk[i] < d.K ? yo[i] : ybytes,
+            NN ? (k0 < d.K ? k0 : 0) * d.ldy * ES : k0 * ES);
+  };
+  uint32_t fa[2], fy[2];
+  const int sw = swz(lane & 31);  // the same for every 32-row block
+#pragma unroll
+  for (int f = 0; f < 2; ++f) {
+    fa[f] = lds_addr(ring) + (32 * f + (lane & 31)) * kDmaRow;
+    if constexpr (NN) {
+      const int si = lane & 15, g = lane >> 4;
+      const int n = 32 * f + 16 * (g & 1) + 4 * (si & 3), kr = 8 * (g >> 1) + (si >> 2);
+      fy[f] = lds_addr(ring) + 4096 + kr * 128 + (((n >> 3) ^ (4 * ((kr >> 1) & 1))) << 4) + 8 * (si & 1);
+    } else {
+      fy[f] = fa[f] + 4096;
+    }
+  }
+  struct Frag {
+    u32x4_t x[2], y[2];
+    u32x2_t l[2], h[2];
+  };
+  auto read = [&](Frag& f, int it, int s) {
+    const uint32_t b = (it % PD) * SLOT, co = ((2 * s + (lane >> 5)) ^ sw) << 4;
+#pragma unroll
+    for (int i = 0; i < 2; ++i) f.x[i] = lds_read16(fa[i] + b + co);
+#pragma unroll
+    for (int j = 0; j < 2; ++j) {
+      if constexpr (NN) {
+        f.l[j] = lds_read8_tr(fy[j] + b + 16 * s * 128);
+        f.h[j] = lds_read8_tr(fy[j] + b + (16 * s + 4) * 128);
+      } else {
+        f.y[j] = lds_read16(fy[j] + b + co);
+      }
+    }
+  };
+  auto wait = [&](Frag& f) {
+    asm volatile("s_waitcnt lgkmcnt(0)" ::: "memory");
+    asm volatile("" : "+v"(f.x[0]), "+v"(f.x[1]));
+    if constexpr (NN) {
+#pragma unroll
+      for (int j = 0; j < 2; ++j) {
+        asm volatile("" : "+v"(f.l[j]), "+v"(f.h[j]));
+        f.y[j] = __builtin_shufflevector(f.l[j], f.h[j], 0, 1, 2, 3);
+      }
+    } else {
+      asm volatile("" : "+v"(f.y[0]), "+v"(f.y[1]));
+    }
+  };
+  f32x16_t acc[2][2];
+#pragma unroll
+  for (int i = 0; i < 2; ++i)
+#pragma unroll
+    for (int j = 0; j < 2; ++j)
+#pragma unroll
+      for (int v = 0; v < 16; ++v) acc[i][j][v] = 0.f;
+  auto math = [&](const Frag& f) {
+#pragma unroll
+    for (int i = 0; i < 2; ++i)
+#pragma unroll
+      for (int j = 0; j < 2; ++j)
+        acc[i][j] = Mfma<bf16>::step(__builtin_bit_cast(uint4, f.x[i]), __builtin_bit_cast(uint4, f.y[j]), acc[i][j]);
+  };
+  Frag f0, f1;
+#pragma unroll
+  for (int p = 0; p < PD; ++p) copy(p);
+  __builtin_amdgcn_s_waitcnt(vmcnt_imm(8 * (PD - 1)));
+  asm volatile("" ::: "memory");
+  read(f0, 0, 0);
+  for (int it = 0; it < nit; ++it) {
+    wait(f0);
+    read(f1, it, 1);
+    __builtin_amdgcn_sched_barrier(0);
+    math(f0);
+    __builtin_amdgcn_sched_barrier(0);
+    wait(f1);
+    copy(it + PD);
+    __builtin_amdgcn_s_waitcnt(vmcnt_imm(8 * (PD - 1)));
+    asm volatile("" ::: "memory");
+    read(f0, it + 1, 0);
+    __builtin_amdgcn_sched_barrier(0);
+    math(f1);
+    __builtin_amdgcn_sched_barrier(0);
+  }
+  wait(f0);
+  // Epilogue.  Wave w finishes the 32 x 32 quadrant (w / 2, w % 2).
+  const int qi = wave >> 1, qj = wave & 1;
+  const int wr0 = m0 + 32 * qi, wc0 = n0 + 32 * qj;
+  const bool mirror = d.Ct != nullptr && !(ti == tj && d.sym);
+  const bool has_d = d.D != nullptr;
+  const uint32_t cbytes = d.C ? uint32_t(d.M) * uint32_t(d.ldc) * ES : 0u;
+  const uint32_t tbytes = mirror ? uint32_t(d.N) * uint32_t(d.ldct) * ES : 0u;
+  const uint32_t dbytes = has_d ? uint32_t(d.N) * uint32_t(d.ldd) * ES : 0u;
+  const __amdgpu_buffer_rsrc_t cr = __builtin_amdgcn_make_buffer_rsrc(d.C ? d.C : d.Ct, 0, cbytes, kBufferWord3);
+  const __amdgpu_buffer_rsrc_t tr = __builtin_amdgcn_make_buffer_rsrc(d.Ct ? d.Ct : d.C, 0, tbytes, kBufferWord3);
+  const __amdgpu_buffer_rsrc_t dr = __builtin_amdgcn_make_buffer_rsrc(
+      const_cast<void*>(has_d ? d.D : d.X), 0, dbytes, kBufferWord3);
+  const int r32 = lane & 31, hi = lane >> 5;
+  u32x2_t dv[4];
+  if (has_d) {
+#pragma unroll
+    for (int v4 = 0; v4 < 4; ++v4) {
+      const int n = wc0 + r32, m = wr0 + 8 * v4 + 4 * hi;
+      dv[v4] = __builtin_amdgcn_raw_buffer_load_b64(dr, n < d.N && m < d.M ? uint32_t(n * d.ldd + m) * ES : dbytes, 0, 0);
+    }
+  }
+  // Zero-filled copies past K may still be in flight into the rings.
+  __builtin_amdgcn_s_waitcnt(vmcnt_imm(0));
+  __syncthreads();
+  f32x4_t* red = reinterpret_cast<f32x4_t*>(lds);
+  unsigned char* st = lds + kRed;
+#pragma unroll
+  for (int q = 0; q < 4; ++q)
+    if (q != wave) {
+#pragma unroll
+      for (int v4 = 0; v4 < 4; ++v4) {
+        f32x4_t x;
+#pragma unroll
+        for (int e = 0; e < 4; ++e) x[e] = acc[q >> 1][q & 1][4 * v4 + e];
+        red[((wave * 4 + q) * 4 + v4) * 64 + lane] = x;
+      }
+    }
+  __syncthreads();
+#pragma unroll
+  for (int v4 = 0; v4 < 4; ++v4) {
+    f32x4_t s[4];
+#pragma unroll
+    for (int w = 0; w < 4; ++w) {
+      if (w == wave) {
+#pragma unroll
+        for (int e = 0; e < 4; ++e) {
+          const int v = 4 * v4 + e;
+          s[w][e] = wave == 0 ? acc[0][0][v] : wave == 1 ? acc[0][1][v] : wave == 2 ? acc[1][0][v] : acc[1][1][v];
+        }
+      } else {
+        s[w] = red[((w * 4 + wave) * 4 + v4) * 64 + lane];
+      }
+    }
+    float y[4];
+#pragma unroll
+    for (int e = 0; e < 4; ++e) y[e] = alpha * ((s[0][e] + s[1][e]) + (s[2][e] + s[3][e]));
+    if (has_d) {
+#pragma unroll
+      for (int h = 0; h < 2; ++h) {
+        y[2 * h] = fmaf(d.beta, __uint_as_float(dv[v4][h] << 16), y[2 * h]);
+        y[2 * h + 1] = fmaf(d.beta, __uint_as_float(dv[v4][h] & 0xffff0000u), y[2 * h + 1]);
+      }
+    }
+    if (d.gamma != 0.f && wr0 == wc0) {
+#pragma unroll
+      for (int e = 0; e < 4; ++e) y[e] += 8 * v4 + 4 * hi + e == r32 ? d.gamma : 0.f;
+    }
+    union {
+      bf16 h[4];
+      u32x2_t v;
+    } u;
+#pragma unroll
+    for (int e = 0; e < 4; ++e) u.h[e] = bf16(y[e]);
+    *reinterpret_cast<u32x2_t*>(st + wave * 2048 + r32 * 64 + ((v4 ^ swz(r32)) << 4) + 8 * hi) = u.v;
+  }
+  asm volatile("" ::: "memory");
+  if (d.C) {
+    const int g = lane >> 4, i = lane & 15;
+    u32x2_t y[2][2];
+#pragma unroll
+    for (int mb = 0; mb < 2; ++mb)
+#pragma unroll
+      for (int k = 0; k < 2; ++k) {
+        const int n = 8 * g + 4 * k + (i >> 2), c = 2 * mb + ((i & 3) >> 1);
+        y[mb][k] = lds_read8_tr(lds_addr(st) + wave * 2048 + n * 64 + ((c ^ swz(n)) << 4) + 8 * (i & 1));
+      }
+    asm volatile("s_waitcnt lgkmcnt(0)" ::: "memory");
+#pragma unroll
+    for (int mb = 0; mb < 2; ++mb) {
+      asm volatile("" : "+v"(y[mb][0]), "+v"(y[mb][1]));
+      const int m = wr0 + 16 * mb + i, n = wc0 + 8 * g;
+      bst16(cr, __builtin_shufflevector(y[mb][0], y[mb][1], 0, 1, 2, 3),
+            m < d.M && n < d.N ? uint32_t(m * d.ldc + n) * ES : cbytes);
+    }
+  }
+  if (mirror) {
+#pragma unroll
+    for (int q = 0; q < 2; ++q) {
+      const int n = 16 * q + (lane >> 2), c = lane & 3;
+      const u32x4_t v = *reinterpret_cast<const u32x4_t*>(st + wave * 2048 + n * 64 + ((c ^ swz(n)) << 4));
+      bst16(tr, v, wc0 + n < d.N && wr0 + 8 * c < d.M ? uint32_t((wc0 + n) * d.ldct + wr0 + 8 * c) * ES : tbytes);
+    }
+  }
+}
+
 // ---------------------------------------------------------------- update
 
 template <typename TP, typename TU, bool VEC, bool NT>
@@ -1701,7 +1960,7 @@ hipError_t launch_ns_gemm(DType ns_t, int variant, bool nn, int n_tiles, const G
                           const TileRef* tiles, int nsplit, float* ksum, int* kcount,
                           hipStream_t s, bool long_k) {
   if (nsplit > 1 && (!ksum || !kcount || !gemm_is_dmap(variant))) return hipErrorInvalidValue;
-  if (nn && !gemm_is_dmap(variant)) return hipErrorInvalidValue;
+  if (nn && !gemm_reads_rows(variant)) return hipErrorInvalidValue;
   if (n_tiles <= 0) return hipSuccess;
   return dispatch1(ns_t, [&](auto n) {
     using TN = decltype(n);
@@ -1759,6 +2018,16 @@ hipError_t launch_ns_gemm(DType ns_t, int variant, bool nn, int n_tiles, const G
             default: MUONBP_DMAP(192, 192, 2, 2); break;
           }
 #undef MUONBP_DMAP
+          break;
+        } else {
+          return hipErrorInvalidValue;
+        }
+      case kGemmWaveK64:
+        if constexpr (std::is_same<TN, bf16>::value) {
+          if (nn)
+            hipLaunchKernelGGL((k_ns_gemm_wavek<true>), dim3(n_tiles), dim3(kThreads), 0, s, probs, tiles);
+          else
+            hipLaunchKernelGGL((k_ns_gemm_wavek<false>), dim3(n_tiles), dim3(kThreads), 0, s, probs, tiles);
           break;
         } else {
           return hipErrorInvalidValue;

@@ -278,10 +278,12 @@ muonbp_status muonbp_describe_plan(const muonbp_matrix* mats, int32_t n_mats,
     return MUONBP_E_DTYPE;
   std::vector<MatrixShape> shapes;
   if (!check_mats(mats, n_mats, &shapes).empty()) return MUONBP_E_INVALID;
-  Layout lay;
+  Layout lay, static_lay;
+  ScratchPlan sp;
   bool shape_err = false;
   try {
-    if (!layout_for(shapes, o, &lay, &shape_err).empty())
+    if (!layout_for(shapes, o, &lay, &shape_err).empty() ||
+        !scratch_layout(shapes, o, full, MUONBP_STATIC_SCRATCH_BYTES, true, &static_lay, &sp, &shape_err).empty())
       return shape_err ? MUONBP_E_SHAPE : MUONBP_E_INVALID;
   } catch (const std::bad_alloc&) {
     return MUONBP_E_NOMEM;
@@ -305,7 +307,7 @@ muonbp_status muonbp_describe_plan(const muonbp_matrix* mats, int32_t n_mats,
   // momentum: read G, M, write M; update: read X, U, write X.
   out->elementwise_bytes = double(lay.total_elems) * ((pb + 2 * sb) + (2 * pb + nb));
   out->workspace_bytes = p.ws_elems * int64_t(nb);
-  out->static_scratch_bytes = scratch_plan(lay, full, o).total;
+  out->static_scratch_bytes = sp.total;
   out->device_bytes = context_bulk_bytes(lay, o);
   for (const Problem& q : p.probs) {
     out->gram_units += q.gram ? 1 : 0;
@@ -314,10 +316,10 @@ muonbp_status muonbp_describe_plan(const muonbp_matrix* mats, int32_t n_mats,
   return MUONBP_OK;
 }
 
-muonbp_status muonbp_create(const muonbp_matrix* mats, int32_t n_mats, int64_t period,
-                            float lr_block, float lr_full, float momentum, float weight_decay,
-                            const muonbp_options* opt, void* hip_stream, muonbp_ctx** out) {
-  if (!out) return MUONBP_E_INVALID;
+// lean: with the plans of layout_for's lean form.
+static muonbp_status create_ctx(const muonbp_matrix* mats, int32_t n_mats, int64_t period, float lr_block,
+                                float lr_full, float momentum, float weight_decay, const muonbp_options* opt,
+                                void* hip_stream, bool lean, muonbp_ctx** out) {
   *out = nullptr;
   muonbp_options o;
   muonbp_options_default(&o);
@@ -336,7 +338,7 @@ muonbp_status muonbp_create(const muonbp_matrix* mats, int32_t n_mats, int64_t p
   if (!c) return MUONBP_E_NOMEM;
   try {
     bool shape_err = false;
-    std::string msg = layout_for(shapes, o, &c->lay, &shape_err);
+    std::string msg = layout_for(shapes, o, &c->lay, &shape_err, true, lean);
     if (!msg.empty()) {
       free_ctx(c);
       return shape_err ? MUONBP_E_SHAPE : MUONBP_E_INVALID;
@@ -411,6 +413,20 @@ muonbp_status muonbp_create(const muonbp_matrix* mats, int32_t n_mats, int64_t p
   if ((e = hipStreamSynchronize(c->stream)) != hipSuccess) return bail(e, "sync");
   *out = c;
   return MUONBP_OK;
+}
+
+muonbp_status muonbp_create(const muonbp_matrix* mats, int32_t n_mats, int64_t period,
+                            float lr_block, float lr_full, float momentum, float weight_decay,
+                            const muonbp_options* opt, void* hip_stream, muonbp_ctx** out) {
+  if (!out) return MUONBP_E_INVALID;
+  muonbp_status st = MUONBP_E_NOMEM;
+  // Out of memory (device_memory_limit, or the device's own): once more with
+  // the smaller plans.
+  for (int lean = 0; lean < 2 && st == MUONBP_E_NOMEM; ++lean) {
+    st = create_ctx(mats, n_mats, period, lr_block, lr_full, momentum, weight_decay, opt, hip_stream, lean != 0, out);
+    if (st == MUONBP_E_NOMEM && lean == 0) (void)hipGetLastError();  // the failed allocation's
+  }
+  return st;
 }
 
 muonbp_status muonbp_step(muonbp_ctx* c, void* const* params, const void* const* grads, int64_t step) {

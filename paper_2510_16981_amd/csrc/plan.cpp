@@ -102,7 +102,7 @@ void append_tiles(const Problem& p, GemmKind kind, int v, int32_t desc,
   int64_t m, c, k;
   gemm_dims(p, kind, &m, &c, &k);
   const int64_t tm = ceil_div(m, kGemmTileRows[v]), tn = ceil_div(c, kGemmTileCols[v]);
-  const bool small_tiles = kGemmTileRows[v] == 128 && v != kGemm128x128Split2;
+  const bool small_tiles = kGemmTileRows[v] <= 128 && v != kGemm128x128Split2;
   const int64_t group = small_tiles || (kind != kGram && tm >= 16) ? 8 : 4;
   for (int64_t g0 = 0; g0 < tm; g0 += group)
     for (int64_t j = (kind == kApply ? 0 : g0); j < tn; ++j)
@@ -270,8 +270,33 @@ double dmap_launch_us(const std::vector<Problem>& probs, GemmKind kind, int v) {
   return double(full) * two + (rest == 0 ? 0.0 : rest <= kNumCUs ? one : two);
 }
 
+// The same for kGemmWaveK64 (two workgroups per CU).  A wave runs a quarter
+// of the slices, so a launch that fits one workgroup per CU is little more
+// than its fixed cost; with more tiles than that, each of which fetches its
+// own operand rows, the time follows the copies.  Measured (us, against the
+// 128 x 128 tiles): 48 tiles of 4 / 16 slices 4.8 / 5.7 (6.1 / 8.2), 30 of 32
+// 6.9 (12.9), 432 of 16 8.7 (10.2), 624 of 24 14.8 (13.1), 640 of 8 10.9
+// (8.5), 528 of 192 79 (59).
+double wave_k_launch_us(const std::vector<Problem>& probs, GemmKind kind) {
+  int64_t tiles = 0;
+  double slices = 0;
+  for (const Problem& p : probs) {
+    int64_t m, c, k;
+    gemm_dims(p, kind, &m, &c, &k);
+    const int64_t tm = ceil_div(m, kGemmTileRows[kGemmWaveK64]), tn = ceil_div(c, kGemmTileCols[kGemmWaveK64]);
+    const int64_t nt = kind == kApply ? tm * tn : tm * (tm + 1) / 2;
+    tiles += nt;
+    slices += double(nt) * double(ceil_div(k, 32));
+  }
+  if (tiles == 0) return 0;
+  slices /= double(tiles);
+  const double one = 2.0 + 0.08 * slices, two = 3.5 + 0.23 * slices;
+  const int64_t full = tiles / (2 * kNumCUs), rest = tiles % (2 * kNumCUs);
+  return 2.4 + double(full) * two + (rest == 0 ? 0.0 : rest <= kNumCUs ? one : two);
+}
+
 int32_t choose_variant(const std::vector<Problem>& probs, GemmKind kind, int tile_policy,
-                       int ns_elem_bytes) {
+                       int ns_elem_bytes, bool wave_k) {
   const bool sym = kind != kApply;
   const bool dma = dma_allowed(probs, kind, ns_elem_bytes);
   if (tile_policy > 0) {
@@ -321,6 +346,9 @@ int32_t choose_variant(const std::vector<Problem>& probs, GemmKind kind, int til
         best_us = us;
       }
     }
+    // The 128 x 128 model above is for full launches: where few CUs are busy
+    // a launch takes 1.5-3 us less, hence the margin.
+    if (wave_k && wave_k_launch_us(probs, kind) < 0.9 * best_us) return kGemmWaveK64;
     if (best == kGemmDmaP192x256) best = kGemmDmaP192x256W8;
     if (best == kGemmDmaP256x192) best = kGemmDmaP256x192W8;
     return best;
@@ -381,7 +409,7 @@ double ns_unit_dense_flops(int64_t S, int64_t L, int K) {
 std::string build_layout(const MatrixShape* mats, int32_t n_mats,
                          int ns_elem_bytes, int ns_steps, int poly_slots, int tile_policy,
                          int k_split, int apply_mode, Layout* out, bool* shape_error, int gram_mode,
-                         bool in_place_input) {
+                         bool in_place_input, bool lean) {
   *shape_error = false;
   if (!mats || n_mats <= 0) return "mats must be a non-empty array";
   if (ns_steps < 0) return "ns_steps must be >= 0";
@@ -501,13 +529,14 @@ std::string build_layout(const MatrixShape* mats, int32_t n_mats,
                "of the NS kernels";
       }
     for (int kind = 0; kind < 3; ++kind) {
-      plan.variant[kind] = choose_variant(plan.probs, GemmKind(kind), tile_policy, ns_elem_bytes);
+      plan.variant[kind] = choose_variant(plan.probs, GemmKind(kind), tile_policy, ns_elem_bytes,
+                                          k_split == 0 && !lean);
       plan.nsplit[kind] = choose_split(plan.probs, GemmKind(kind), plan.variant[kind], k_split);
       plan.tiles_per_iter[kind] = count_tiles(plan.probs, GemmKind(kind), plan.variant[kind]);
       if (plan.tiles_per_iter[kind] * plan.nsplit[kind] > int64_t(std::numeric_limits<int32_t>::max() / 2))
         return "too many tiles";
     }
-    plan.nn_apply = apply_mode == 0 && gemm_is_dmap(plan.variant[kApply]);
+    plan.nn_apply = apply_mode == 0 && gemm_reads_rows(plan.variant[kApply]);
     int64_t cursor = 0;
     for (int32_t pi = 0; pi < int32_t(plan.probs.size()); ++pi) {
       Problem& p = plan.probs[pi];

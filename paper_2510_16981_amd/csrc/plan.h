@@ -171,11 +171,14 @@ struct Layout {
 // dtype (bf16 state, bf16 NS, no Nesterov blend); untransposed units whose
 // momentum window is 16-byte aligned then read it in place
 // (Problem::in_place).
+// lean: the plan with the smallest tables and workspace, for callers whose
+// memory limit the faster one exceeds (no kGemmWaveK64: its 64 x 64 tiles
+// have longer tile lists).
 std::string build_layout(const MatrixShape* mats, int32_t n_mats,
                          int ns_elem_bytes, int ns_steps, int poly_slots, int tile_policy,
                          int k_split, int apply_mode,
                          Layout* out, bool* shape_error, int gram_mode = 0,
-                         bool in_place_input = false);
+                         bool in_place_input = false, bool lean = false);
 
 // Descriptor slot of segment sg's apply on a Gram-space unit (Z[1 - z] =
 // Q[q] Z[z] with z = sg mod 2, q the buffer of the segment's last Q, and
@@ -183,9 +186,10 @@ std::string build_layout(const MatrixShape* mats, int32_t n_mats,
 int32_t gram_apply_slot(int ns_steps, int sg);
 int32_t first_apply_slot(const Problem& p, int ns_steps);
 
-// Tile shape the planner picks for one grouped product.
+// Tile shape the planner picks for one grouped product (wave_k: kGemmWaveK64
+// may be picked).
 int32_t choose_variant(const std::vector<Problem>& probs, GemmKind kind, int tile_policy,
-                       int ns_elem_bytes);
+                       int ns_elem_bytes, bool wave_k = false);
 
 int32_t choose_split(const std::vector<Problem>& probs, GemmKind kind, int32_t variant,
                      int k_split);

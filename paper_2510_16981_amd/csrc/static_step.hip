@@ -100,9 +100,10 @@ extern "C" muonbp_status muonbp_step_static(const muonbp_matrix* mats, int32_t n
   std::vector<BlockDesc> bd;
   try {
     bool shape_err = false;
-    if (!layout_for(shapes, o, &lay, &shape_err, reinterpret_cast<uintptr_t>(momentum) % 16 == 0).empty())
+    if (!scratch_layout(shapes, o, full, kStaticScratchBytes, reinterpret_cast<uintptr_t>(momentum) % 16 == 0, &lay,
+                        &sp, &shape_err)
+             .empty())
       return shape_err ? MUONBP_E_SHAPE : MUONBP_E_INVALID;
-    sp = scratch_plan(lay, full, o);
     if (sp.total > kStaticScratchBytes) return MUONBP_E_TOO_LARGE;
     bd = block_descs(lay);
   } catch (const std::bad_alloc&) {

@@ -35,9 +35,10 @@ std::string check_mats(const muonbp_matrix* mats, int32_t n_mats, std::vector<Ma
 
 // build_layout with the NS settings of the options.  momentum_aligned: the
 // momentum arena starts on a 16-byte boundary (always for a context's own
-// arena), a condition for reading it in place as the NS input.
+// arena), a condition for reading it in place as the NS input.  lean: as
+// build_layout has it.
 std::string layout_for(const std::vector<MatrixShape>& shapes, const muonbp_options& o, Layout* out,
-                       bool* shape_error, bool momentum_aligned = true);
+                       bool* shape_error, bool momentum_aligned = true, bool lean = false);
 
 // Host form of one plan's device tables, the NS workspace starting at `ws`,
 // the momentum arena at `mom` and the per-problem scales at `scales` (both
@@ -71,6 +72,11 @@ struct ScratchPlan {
   int64_t total = 0;
 };
 ScratchPlan scratch_plan(const Layout& lay, int full, const muonbp_options& o);
+
+// The allocation-free step's layout and scratch plan: layout_for's, or its
+// lean form where only that fits `limit` bytes.
+std::string scratch_layout(const std::vector<MatrixShape>& shapes, const muonbp_options& o, int full,
+                           int64_t limit, bool momentum_aligned, Layout* lay, ScratchPlan* sp, bool* shape_error);
 
 // Device view of one plan's tables.
 struct PlanView {
