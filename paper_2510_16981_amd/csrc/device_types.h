@@ -88,15 +88,18 @@ enum GemmVariant : int32_t {
   kGemmDmaP192x256 = 10, kGemmDmaP256x192 = 11, kGemmDmaP192x192 = 12,
   kGemmDmaP256x256W8 = 13, kGemmDmaP192x256W8 = 14, kGemmDmaP256x192W8 = 15,
   kNumGemmVariants = 16,  // the variants muonbp_options.tile_policy can name
-  kGemmWaveK64 = 16,      // chosen by the planner only
-  kNumGemmKernels = 17
+  // Chosen by the planner only:
+  kGemmWaveK64 = 16,
+  kGemmF32x128 = 17, kGemmF32x64 = 18,  // fp32 operands as three bf16 parts
+  kGemmF32WaveK32 = 19,                 // the same, K slices shared by the waves
+  kNumGemmKernels = 20
 };
 constexpr int kGemmTileRows[kNumGemmKernels] = {128, 256, 256, 128, 256, 256, 128, 128, 256,
-                                                256, 192, 256, 192, 256, 192, 256, 64};
+                                                256, 192, 256, 192, 256, 192, 256, 64,  128, 64,  32};
 constexpr int kGemmTileCols[kNumGemmKernels] = {128, 128, 256, 128, 128, 256, 128, 128, 128,
-                                                256, 256, 192, 192, 256, 256, 192, 64};
+                                                256, 256, 192, 192, 256, 256, 192, 64,  128, 64,  32};
 constexpr bool kGemmIsDma[kNumGemmKernels] = {false, false, false, true, true, true, false, true, true,
-                                              true,  true,  true,  true, true, true, true,  true};
+                                              true,  true,  true,  true, true, true, true,  true, false, false, false};
 // Interleaved DMA kernels (k_ns_gemm_dmap).
 constexpr bool gemm_is_dmap(int v) { return v >= kGemmDmaP128x128 && v <= kGemmDmaP256x192W8; }
 // Kernels whose apply can read Z row-major.

@@ -38,6 +38,11 @@ __device__ __forceinline__ void gstore1(T* p, T v) {
   *(__attribute__((address_space(1))) T*)(reinterpret_cast<uintptr_t>(p)) = v;
 }
 
+template <typename T>
+__device__ __forceinline__ T gload1(const T* p) {
+  return *(const __attribute__((address_space(1))) T*)(reinterpret_cast<uintptr_t>(p));
+}
+
 constexpr int kThreads = 256;
 
 // ---------------------------------------------------------------- helpers
@@ -1686,6 +1691,313 @@ __global__ __launch_bounds__(kThreads) void k_ns_gemm_wavek(const GemmDesc* __re
   }
 }
 
+// ---------------------------------------------------------------- NS GEMM, fp32 operands as three bf16 parts
+//
+// The fp32 matrix instruction runs at 1/16 of the bf16 rate.  An fp32 value is
+// exactly the sum of three bf16 parts of 8 significant bits each (rounded to
+// nearest, h = bf16(x), m = bf16(x - h), l = x - h - m), products of parts are
+// exact in fp32, and of the nine the three below 2^-24 of x y (m l, l m, l l)
+// are left out: six bf16 MFMAs of 16 K columns in place of eight fp32 ones of
+// 2, at 2.7 times their rate.  Sums stay in fp32; the smaller products have
+// accumulators of their own, added once at the end.  Against 64 bits U is
+// closer than with fp32 products: 5.6e-7 against 1.1e-6 (1000 x 1333), 7.2e-7
+// against 1.4e-6 (2048 x 2048), 3.1e-7 against 1.1e-6 (300 x 40000).
+//
+// Tile BM x BM, 4 waves in a 2 x 2 layout.  The K loop loads 32 K columns of X
+// and Y rows (128 bytes a row) into registers a slice ahead of their use,
+// splits them between the MFMAs of the current slice (5.5 VALU instructions per
+// element, hidden in the MFMAs' shadow) and stores the parts in one of two LDS
+// stages: three planes of 64-byte rows, 16-byte chunk c of row r at c ^ swz(r).
+// A 128 x 128 tile takes 1.0 us a slice alone (0.65 of it MFMA), the apply of 8
+// units of 2048 x 2048 runs at 179 TFLOP/s (fp32 MFMA kernels: 65-80), a
+// launch of few tiles is fixed cost: 10 us, 6.7 with 64 x 64 tiles.
+// Two fp32 values to a word of bf16 (round to nearest even).
+typedef float f32x2_t __attribute__((ext_vector_type(2)));
+typedef __bf16 bf16x2_t __attribute__((ext_vector_type(2)));
+__device__ __forceinline__ uint32_t pack2(float a, float b) {
+  return __builtin_bit_cast(uint32_t, __builtin_convertvector(f32x2_t{a, b}, bf16x2_t));
+}
+__device__ __forceinline__ void split3(const uint4& v, u32x2_t& h, u32x2_t& m, u32x2_t& l) {
+  const float x[4] = {__uint_as_float(v.x), __uint_as_float(v.y), __uint_as_float(v.z), __uint_as_float(v.w)};
+#pragma unroll
+  for (int e = 0; e < 2; ++e) {
+    const uint32_t a = pack2(x[2 * e], x[2 * e + 1]);
+    const float r0 = x[2 * e] - __uint_as_float(a << 16), r1 = x[2 * e + 1] - __uint_as_float(a & 0xffff0000u);
+    const uint32_t b = pack2(r0, r1);
+    h[e] = a;
+    m[e] = b;
+    l[e] = pack2(r0 - __uint_as_float(b << 16), r1 - __uint_as_float(b & 0xffff0000u));
+  }
+}
+
+template <int BM>
+__global__ __launch_bounds__(kThreads) void k_ns_gemm_f32(const GemmDesc* __restrict__ probs,
+                                                          const TileRef* __restrict__ tiles) {
+  constexpr int TM = BM / 64, Q = BM / 32, ES = 4, BK = 32;
+  constexpr int PLANE = 2 * BM * kDmaRow, STAGE = 3 * PLANE;
+  constexpr int EPI = 4 * 32 * (32 * TM + 1) * 4;
+  static_assert(2 * STAGE >= EPI, "the epilogue stages in the slices' LDS");
+  __shared__ __attribute__((aligned(16))) unsigned char lds[2 * STAGE];
+  const TileRef t = tiles[blockIdx.x];
+  const GemmDesc d = probs[t.prob];
+  const float alpha = desc_alpha(d);
+  const int ti = t.ij >> 16, tj = t.ij & 0xffff;
+  const int m0 = ti * BM, n0 = tj * BM;
+  const int tid = threadIdx.x, lane = tid & 63, wave = tid >> 6;
+  const int wm = wave >> 1, wn = wave & 1;
+  const int xbytes = d.M * d.ldx * ES, ybytes = d.N * d.ldy * ES;
+  const __amdgpu_buffer_rsrc_t xr =
+      __builtin_amdgcn_make_buffer_rsrc(const_cast<void*>(d.X), 0, xbytes, kBufferWord3);
+  const __amdgpu_buffer_rsrc_t yr =
+      __builtin_amdgcn_make_buffer_rsrc(const_cast<void*>(d.Y), 0, ybytes, kBufferWord3);
+  // This thread's chunk (4 columns) of rows tid / 8 + 32 q; rows past M (N)
+  // and columns past K as in k_ns_gemm.
+  const int kc = (tid & 7) * 4;
+  int vo[2 * Q];
+#pragma unroll
+  for (int q = 0; q < Q; ++q) {
+    const int m = m0 + (tid >> 3) + 32 * q, n = n0 + (tid >> 3) + 32 * q;
+    vo[q] = m < d.M ? (m * d.ldx + kc) * ES : xbytes;
+    vo[Q + q] = n < d.N ? (n * d.ldy + kc) * ES : ybytes;
+  }
+  uint4 raw[2 * Q];
+  // TAIL: the slice may reach past K.
+  auto fetch = [&](auto tail, int kt, int q) {
+    const int k0 = kt * BK;
+    const __amdgpu_buffer_rsrc_t r = q < Q ? xr : yr;
+    if constexpr (!decltype(tail)::value) {
+      raw[q] = bld16(r, vo[q], k0 * ES);
+    } else {
+      const int nv = max(0, min(d.K - (k0 + kc), 4));
+      raw[q] = mask_tail<float>(bld16(r, nv > 0 ? vo[q] : (q < Q ? xbytes : ybytes), k0 * ES), nv);
+    }
+  };
+  auto put = [&](int buf, int q) {
+    const int row = (q < Q ? 0 : BM) + (tid >> 3) + 32 * (q % Q), u = tid & 7;
+    u32x2_t* p = reinterpret_cast<u32x2_t*>(lds + buf * STAGE + row * kDmaRow + (((u >> 1) ^ swz(row)) << 4) + 8 * (u & 1));
+    u32x2_t h, m, l;
+    split3(raw[q], h, m, l);
+    p[0] = h;
+    p[PLANE / 8] = m;
+    p[2 * PLANE / 8] = l;
+  };
+  struct Frag {
+    uint4 x[3][TM], y[3][TM];
+  };
+  const int sw = swz(lane & 31);
+  const unsigned char* fx = lds + (wm * 32 * TM + (lane & 31)) * kDmaRow;
+  const unsigned char* fy = lds + (BM + wn * 32 * TM + (lane & 31)) * kDmaRow;
+  auto read = [&](Frag& f, int buf, int s) {
+    const int o = buf * STAGE + (((2 * s + (lane >> 5)) ^ sw) << 4);
+#pragma unroll
+    for (int p = 0; p < 3; ++p)
+#pragma unroll
+      for (int i = 0; i < TM; ++i) {
+        f.x[p][i] = *reinterpret_cast<const uint4*>(fx + o + p * PLANE + i * 32 * kDmaRow);
+        f.y[p][i] = *reinterpret_cast<const uint4*>(fy + o + p * PLANE + i * 32 * kDmaRow);
+      }
+  };
+  f32x16_t acc[TM][TM], low[TM][TM];
+#pragma unroll
+  for (int i = 0; i < TM; ++i)
+#pragma unroll
+    for (int j = 0; j < TM; ++j)
+#pragma unroll
+      for (int v = 0; v < 16; ++v) acc[i][j][v] = low[i][j][v] = 0.f;
+  // Product o of the six, all TM x TM tiles: h l, l h, m m, h m, m h, h h.
+  auto math = [&](const Frag& f, int o) {
+    constexpr int PX[6] = {0, 2, 1, 0, 1, 0}, PY[6] = {2, 0, 1, 1, 0, 0};
+#pragma unroll
+    for (int i = 0; i < TM; ++i)
+#pragma unroll
+      for (int j = 0; j < TM; ++j) {
+        f32x16_t& c = o < 5 ? low[i][j] : acc[i][j];
+        c = Mfma<bf16>::step(f.x[PX[o]][i], f.y[PY[o]][j], c);
+      }
+  };
+  // Order of one product's MFMAs and the splitting of n chunks: a share of the
+  // VALU work behind each MFMA, as much as fits its 32 clocks.
+  auto interleave = [&](auto n) {
+    constexpr int VALU = 24 * decltype(n)::value;
+#pragma unroll
+    for (int q = 0; q < TM * TM; ++q) {
+      __builtin_amdgcn_sched_group_barrier(0x008, 1, 0);
+      if constexpr (VALU > 0) __builtin_amdgcn_sched_group_barrier(0x002, (VALU + TM * TM - 1) / (TM * TM), 0);
+    }
+    __builtin_amdgcn_sched_barrier(0);
+  };
+  const int nk = (d.K + BK - 1) / BK;
+#pragma unroll
+  for (int q = 0; q < 2 * Q; ++q) fetch(std::true_type{}, 0, q);
+#pragma unroll
+  for (int q = 0; q < 2 * Q; ++q) {
+    put(0, q);
+    fetch(std::true_type{}, 1, q);
+  }
+  __syncthreads();
+  Frag f0, f1;
+  read(f0, 0, 0);
+  auto slice = [&](auto tail, int kt) {
+    const int buf = kt & 1;
+    read(f1, buf, 1);
+    __builtin_amdgcn_sched_barrier(0);
+    // Half of the next slice is split and stored under each K step's MFMAs,
+    // each register refilled with the slice after it.
+    auto part = [&](auto step, auto prod) {
+      constexpr int s = decltype(step)::value, o = decltype(prod)::value, N = s == 0 ? 6 : 4;
+      constexpr int lo = o * Q / N, hi = (o + 1) * Q / N;
+      math(s == 0 ? f0 : f1, o);
+#pragma unroll
+      for (int q = lo; q < hi; ++q) {
+        put(buf ^ 1, s * Q + q);
+        fetch(tail, kt + 2, s * Q + q);
+      }
+      interleave(std::integral_constant<int, hi - lo>{});
+    };
+    using I0 = std::integral_constant<int, 0>;
+    using I1 = std::integral_constant<int, 1>;
+    using I2 = std::integral_constant<int, 2>;
+    using I3 = std::integral_constant<int, 3>;
+    part(I0{}, I0{});
+    part(I0{}, I1{});
+    part(I0{}, I2{});
+    part(I0{}, I3{});
+    part(I0{}, std::integral_constant<int, 4>{});
+    part(I0{}, std::integral_constant<int, 5>{});
+    part(I1{}, I0{});
+    part(I1{}, I1{});
+    part(I1{}, I2{});
+    part(I1{}, I3{});
+    // Slice kt + 1 is stored by every wave, and no wave reads slice kt any
+    // more; its first K step is read under the last two products.
+    asm volatile("s_waitcnt lgkmcnt(0)\n\ts_barrier" ::: "memory");
+    read(f0, buf ^ 1, 0);
+    __builtin_amdgcn_sched_barrier(0);
+    math(f1, 4);
+    math(f1, 5);
+  };
+  int kt = 0;
+  for (; kt < nk - 3; ++kt) slice(std::false_type{}, kt);  // fetches up to slice nk - 2
+  for (; kt < nk; ++kt) slice(std::true_type{}, kt);
+#pragma unroll
+  for (int i = 0; i < TM; ++i)
+#pragma unroll
+    for (int j = 0; j < TM; ++j) acc[i][j] += low[i][j];
+  __syncthreads();
+  gemm_epilogue<float, TM, TM>(acc, reinterpret_cast<float*>(lds) + wave * 32 * (32 * TM + 1), d, m0, n0,
+                               ti == tj && d.sym, alpha, d.beta, d.gamma);
+}
+
+// The same split for launches of few tiles: 32 x 32 tiles, each of the four
+// waves running every fourth 32-column K slice of the whole tile from its own
+// registers.  A lane loads the eight K columns that its MFMA operand holds
+// (row lane % 32, columns 8 (lane / 32) .. + 7 of each 16), so the loop has
+// neither LDS nor barriers; its loads, 16 bytes in each of 32 rows, cost four
+// times a coalesced one, which is why only launches that the tiles above
+// would leave most CUs idle for take it.  Measured per launch: one 256 x 256
+// unit 8.2 us against 11.0 on 64 x 64 tiles (fp32 MFMA: 26), a Gram of 128 x
+// 4096 42 against 69 us, 1024 x 1024 32 against 24.
+__global__ __launch_bounds__(kThreads) void k_ns_gemm_f32_wavek(const GemmDesc* __restrict__ probs,
+                                                                const TileRef* __restrict__ tiles) {
+  constexpr int T = 32, PD = 2, ES = 4, BK = 32;
+  __shared__ __attribute__((aligned(16))) float red[4][16][64];
+  const TileRef t = tiles[blockIdx.x];
+  const GemmDesc d = probs[t.prob];
+  const float alpha = desc_alpha(d);
+  const int ti = t.ij >> 16, tj = t.ij & 0xffff;
+  const int m0 = ti * T, n0 = tj * T;
+  const int lane = threadIdx.x & 63, r32 = lane & 31, hi = lane >> 5;
+  const int wave = __builtin_amdgcn_readfirstlane(threadIdx.x >> 6);
+  const int xbytes = d.M * d.ldx * ES, ybytes = d.N * d.ldy * ES;
+  const __amdgpu_buffer_rsrc_t xr =
+      __builtin_amdgcn_make_buffer_rsrc(const_cast<void*>(d.X), 0, xbytes, kBufferWord3);
+  const __amdgpu_buffer_rsrc_t yr =
+      __builtin_amdgcn_make_buffer_rsrc(const_cast<void*>(d.Y), 0, ybytes, kBufferWord3);
+  const int xo = m0 + r32 < d.M ? ((m0 + r32) * d.ldx + 8 * hi) * ES : xbytes;
+  const int yo = n0 + r32 < d.N ? ((n0 + r32) * d.ldy + 8 * hi) * ES : ybytes;
+  const int nk = (d.K + BK - 1) / BK;
+  const int nit = nk > wave ? (nk - wave + 3) / 4 : 0;  // this wave's slices: wave, wave + 4, ..
+  // Chunk c (4 columns) of this lane's slice: columns 16 (c / 2) + 8 hi + 4 (c % 2).
+  uint4 xa[PD][4], ya[PD][4];
+  auto fetch = [&](int it, int p) {
+    const int k0 = BK * (wave + 4 * it);
+#pragma unroll
+    for (int c = 0; c < 4; ++c) {
+      const int co = 16 * (c >> 1) + 4 * (c & 1);
+      const int nv = it < nit ? max(0, min(d.K - (k0 + co + 8 * hi), 4)) : 0;
+      xa[p][c] = mask_tail<float>(bld16(xr, nv > 0 ? xo + co * ES : xbytes, k0 * ES), nv);
+      ya[p][c] = mask_tail<float>(bld16(yr, nv > 0 ? yo + co * ES : ybytes, k0 * ES), nv);
+    }
+  };
+  f32x16_t acc, low;
+#pragma unroll
+  for (int v = 0; v < 16; ++v) acc[v] = low[v] = 0.f;
+#pragma unroll
+  for (int p = 0; p < PD; ++p) fetch(p, p);
+  for (int it = 0; it < nit; it += PD) {
+#pragma unroll
+    for (int p = 0; p < PD; ++p) {
+      if (it + p >= nit) break;  // uniform
+#pragma unroll
+      for (int s = 0; s < 2; ++s) {
+        u32x2_t x[2][3], y[2][3];
+#pragma unroll
+        for (int c = 0; c < 2; ++c) {
+          split3(xa[p][2 * s + c], x[c][0], x[c][1], x[c][2]);
+          split3(ya[p][2 * s + c], y[c][0], y[c][1], y[c][2]);
+        }
+        uint4 fx[3], fy[3];
+#pragma unroll
+        for (int q = 0; q < 3; ++q) {
+          fx[q] = make_uint4(x[0][q][0], x[0][q][1], x[1][q][0], x[1][q][1]);
+          fy[q] = make_uint4(y[0][q][0], y[0][q][1], y[1][q][0], y[1][q][1]);
+        }
+        low = Mfma<bf16>::step(fx[0], fy[2], low);
+        acc = Mfma<bf16>::step(fx[0], fy[0], acc);
+        low = Mfma<bf16>::step(fx[2], fy[0], low);
+        low = Mfma<bf16>::step(fx[1], fy[1], low);
+        low = Mfma<bf16>::step(fx[0], fy[1], low);
+        low = Mfma<bf16>::step(fx[1], fy[0], low);
+      }
+      fetch(it + p + PD, p);
+    }
+  }
+  acc += low;
+#pragma unroll
+  for (int v = 0; v < 16; ++v) red[wave][v][lane] = acc[v];
+  __syncthreads();
+  // Wave w finishes the accumulators 4 w .. + 3: rows 8 w + 4 hi + e of column
+  // r32 of the tile, four consecutive elements of a row of Ct.
+  float f[4];
+#pragma unroll
+  for (int e = 0; e < 4; ++e) {
+    const int v = 4 * wave + e;
+    f[e] = alpha * ((red[0][v][lane] + red[1][v][lane]) + (red[2][v][lane] + red[3][v][lane]));
+  }
+  const int n = n0 + r32, m = m0 + 8 * wave + 4 * hi;
+  const bool mirror = d.Ct != nullptr && !(ti == tj && d.sym);
+#pragma unroll
+  for (int e = 0; e < 4; ++e) {
+    if (m + e < d.M && n < d.N) {
+      if (d.D) f[e] = fmaf(d.beta, gload1(static_cast<const float*>(d.D) + int64_t(m + e) * d.ldd + n), f[e]);
+      if (m + e == n) f[e] += d.gamma;
+      if (d.C) gstore1(static_cast<float*>(d.C) + int64_t(m + e) * d.ldc + n, f[e]);
+    }
+  }
+  if (mirror && n < d.N) {
+    float* p = static_cast<float*>(d.Ct) + int64_t(n) * d.ldct + m;
+    if (m + 4 <= d.M) {
+      u32x4_t v;
+#pragma unroll
+      for (int e = 0; e < 4; ++e) v[e] = __float_as_uint(f[e]);
+      *gvec(p) = v;
+    } else {
+      for (int e = 0; e < 4; ++e)
+        if (m + e < d.M) gstore1(p + e, f[e]);
+    }
+  }
+}
+
 // ---------------------------------------------------------------- update
 
 template <typename TP, typename TU, bool VEC, bool NT>
@@ -2028,6 +2340,20 @@ hipError_t launch_ns_gemm(DType ns_t, int variant, bool nn, int n_tiles, const G
             hipLaunchKernelGGL((k_ns_gemm_wavek<true>), dim3(n_tiles), dim3(kThreads), 0, s, probs, tiles);
           else
             hipLaunchKernelGGL((k_ns_gemm_wavek<false>), dim3(n_tiles), dim3(kThreads), 0, s, probs, tiles);
+          break;
+        } else {
+          return hipErrorInvalidValue;
+        }
+      case kGemmF32x128:
+      case kGemmF32x64:
+      case kGemmF32WaveK32:
+        if constexpr (std::is_same<TN, float>::value) {
+          if (variant == kGemmF32WaveK32)
+            hipLaunchKernelGGL((k_ns_gemm_f32_wavek), dim3(n_tiles), dim3(kThreads), 0, s, probs, tiles);
+          else if (variant == kGemmF32x128)
+            hipLaunchKernelGGL((k_ns_gemm_f32<128>), dim3(n_tiles), dim3(kThreads), 0, s, probs, tiles);
+          else
+            hipLaunchKernelGGL((k_ns_gemm_f32<64>), dim3(n_tiles), dim3(kThreads), 0, s, probs, tiles);
           break;
         } else {
           return hipErrorInvalidValue;

@@ -295,8 +295,38 @@ double wave_k_launch_us(const std::vector<Problem>& probs, GemmKind kind) {
   return 2.4 + double(full) * two + (rest == 0 ? 0.0 : rest <= kNumCUs ? one : two);
 }
 
+// The kernel of one fp32 launch, by time models of the three tile shapes whose
+// operands are split into bf16 parts, in us: 128 x 128 tiles, one per CU at a
+// time, 8 + 1.2 a 32-column slice each; 64 x 64 tiles, 6.7 a launch and 0.46 a
+// slice (0.5 alone on a CU); 32 x 32 tiles with the slices shared by the
+// waves, 5.7 a launch and 0.29 a slice.  Measured at 128 / 64 / 32: one 256 x
+// 256 unit 20 / 11 / 8, one 1024 x 1024 45 / 24 / 32, 144 tiles of 128 at K =
+// 4096 155 / 155 / 274, 1088 at K = 2048 443 / 464 / 988.  -1: a product over
+// more than kLongK terms, which takes the kernel that restarts its sums.
+int32_t f32_split_variant(const std::vector<Problem>& probs, GemmKind kind) {
+  int64_t tiles[3] = {0, 0, 0};
+  static const int32_t variant[3] = {kGemmF32x128, kGemmF32x64, kGemmF32WaveK32};
+  double slices = 0;
+  for (const Problem& p : probs) {
+    int64_t m, c, k;
+    gemm_dims(p, kind, &m, &c, &k);
+    if (k > kLongK) return -1;
+    for (int v = 0; v < 3; ++v) {
+      const int64_t tm = ceil_div(m, kGemmTileRows[variant[v]]), tn = ceil_div(c, kGemmTileCols[variant[v]]);
+      const int64_t nt = kind == kApply ? tm * tn : tm * (tm + 1) / 2;
+      tiles[v] += nt;
+      if (v == 0) slices += double(nt) * double(ceil_div(k, 32));
+    }
+  }
+  slices /= double(tiles[0]);
+  auto per_cu = [&](int v) { return std::max(1.0, double(tiles[v]) / kNumCUs); };
+  const double us[3] = {double(ceil_div(tiles[0], kNumCUs)) * (8 + 1.2 * slices),
+                        6.7 + std::max(0.5, 0.46 * per_cu(1)) * slices, 5.7 + 0.29 * per_cu(2) * slices};
+  return variant[std::min_element(us, us + 3) - us];
+}
+
 int32_t choose_variant(const std::vector<Problem>& probs, GemmKind kind, int tile_policy,
-                       int ns_elem_bytes, bool wave_k) {
+                       int ns_elem_bytes, bool wave_k, bool lean) {
   const bool sym = kind != kApply;
   const bool dma = dma_allowed(probs, kind, ns_elem_bytes);
   if (tile_policy > 0) {
@@ -354,6 +384,10 @@ int32_t choose_variant(const std::vector<Problem>& probs, GemmKind kind, int til
     return best;
   }
   const int64_t n128 = count_tiles(probs, kind, kGemm128x128);
+  if (ns_elem_bytes == 4 && !lean) {
+    const int32_t v = f32_split_variant(probs, kind);
+    if (v >= 0) return v;
+  }
   const int32_t small = n128 < 2 * kNumCUs ? kGemm128x128Split2 : kGemm128x128;
   if (sym) return small;
   if (count_tiles(probs, kind, kGemm256x256) >= 2 * kNumCUs) return kGemm256x256;
@@ -530,7 +564,7 @@ std::string build_layout(const MatrixShape* mats, int32_t n_mats,
       }
     for (int kind = 0; kind < 3; ++kind) {
       plan.variant[kind] = choose_variant(plan.probs, GemmKind(kind), tile_policy, ns_elem_bytes,
-                                          k_split == 0 && !lean);
+                                          k_split == 0 && !lean, lean);
       plan.nsplit[kind] = choose_split(plan.probs, GemmKind(kind), plan.variant[kind], k_split);
       plan.tiles_per_iter[kind] = count_tiles(plan.probs, GemmKind(kind), plan.variant[kind]);
       if (plan.tiles_per_iter[kind] * plan.nsplit[kind] > int64_t(std::numeric_limits<int32_t>::max() / 2))

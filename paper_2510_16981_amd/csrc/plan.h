@@ -172,8 +172,8 @@ struct Layout {
 // momentum window is 16-byte aligned then read it in place
 // (Problem::in_place).
 // lean: the plan with the smallest tables and workspace, for callers whose
-// memory limit the faster one exceeds (no kGemmWaveK64: its 64 x 64 tiles
-// have longer tile lists).
+// memory limit the faster one exceeds (none of the kernels only the planner
+// can choose: their smaller tiles have longer tile lists).
 std::string build_layout(const MatrixShape* mats, int32_t n_mats,
                          int ns_elem_bytes, int ns_steps, int poly_slots, int tile_policy,
                          int k_split, int apply_mode,
@@ -187,9 +187,9 @@ int32_t gram_apply_slot(int ns_steps, int sg);
 int32_t first_apply_slot(const Problem& p, int ns_steps);
 
 // Tile shape the planner picks for one grouped product (wave_k: kGemmWaveK64
-// may be picked).
+// may be picked; lean: no kernel beyond those tile_policy can name).
 int32_t choose_variant(const std::vector<Problem>& probs, GemmKind kind, int tile_policy,
-                       int ns_elem_bytes, bool wave_k = false);
+                       int ns_elem_bytes, bool wave_k = false, bool lean = false);
 
 int32_t choose_split(const std::vector<Problem>& probs, GemmKind kind, int32_t variant,
                      int k_split);
