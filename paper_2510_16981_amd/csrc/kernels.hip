@@ -149,9 +149,34 @@ template <bool NT> __device__ __forceinline__ void store8r(float* p, const float
   }
 }
 
+// Eight consecutive elements at any element address (the hardware takes
+// unaligned vector accesses; a chunk may then touch one more cache line).
+typedef __attribute__((address_space(1))) u32x4_t g_u32x4_a2_t __attribute__((aligned(2)));
+typedef __attribute__((address_space(1))) u32x4_t g_u32x4_a4_t __attribute__((aligned(4)));
+template <typename T> using g_unaligned_t = std::conditional_t<sizeof(T) == 2, g_u32x4_a2_t, g_u32x4_a4_t>;
+template <typename T> __device__ __forceinline__ Raw8<T> load8u(const T* p) {
+  Raw8<T> r;
+  g_unaligned_t<T>* q = (g_unaligned_t<T>*)(reinterpret_cast<uintptr_t>(p));
+#pragma unroll
+  for (int i = 0; i < int(sizeof(T) / 2); ++i) r.w[i] = q[i];
+  return r;
+}
+template <typename T> __device__ __forceinline__ void store8u(T* p, const float f[8]) {
+  g_unaligned_t<T>* q = (g_unaligned_t<T>*)(reinterpret_cast<uintptr_t>(p));
+  union {
+    T h[8];
+    u32x4_t v[sizeof(T) / 2];
+  } u;
+#pragma unroll
+  for (int i = 0; i < 8; ++i) u.h[i] = from_f<T>(f[i]);
+#pragma unroll
+  for (int i = 0; i < int(sizeof(T) / 2); ++i) q[i] = u.v[i];
+}
+
 // Chunks of 8 elements each thread of an elementwise kernel loads before it
 // does any arithmetic (memory-level parallelism of the streaming loops).
 constexpr int kStreamUnroll = 8;
+constexpr int kUnalignedUnroll = 4;  // the same where chunks have any alignment
 
 // Deterministic workgroup sum (fixed butterfly inside each wave, fixed
 // wave order across the workgroup).
@@ -217,15 +242,52 @@ __global__ __launch_bounds__(kThreads) void k_momentum(
       }
     }
   } else {
-    const int n = sd.nrows * cols;
-    for (int e = threadIdx.x; e < n; e += kThreads) {
-      const int r = e / cols;
-      const int64_t o = int64_t(r) * bd.ld + (e - r * cols);
-      const float gv = to_f<TG>(g[o]);
-      const float mv = rt<TM>(fmaf(mu, to_f<TM>(m[o]), gv));
-      m[o] = from_f<TM>(mv);
-      const float y = nesterov ? fmaf(mu, mv, gv) : mv;
-      acc = fmaf(y, y, acc);
+    // Any size and alignment: chunks of 8 elements of a row (of the whole
+    // segment where its rows are contiguous) at whatever address they have,
+    // the row's last partial chunk element by element.
+    const bool flat = bd.ld == cols;
+    const int rows = flat ? 1 : sd.nrows, rc = flat ? sd.nrows * cols : cols;
+    const int cpr = (rc + 7) >> 3, nc = rows * cpr;
+    for (int c0 = threadIdx.x; c0 < nc; c0 += kThreads * kUnalignedUnroll) {
+      Raw8<TG> gr[kUnalignedUnroll];
+      Raw8<TM> mr[kUnalignedUnroll];
+      int64_t o[kUnalignedUnroll];
+      int left[kUnalignedUnroll];  // elements of the chunk
+#pragma unroll
+      for (int u = 0; u < kUnalignedUnroll; ++u) {
+        const int c = c0 + kThreads * u, r = c / cpr, k = (c - r * cpr) << 3;
+        o[u] = int64_t(r) * bd.ld + k;
+        left[u] = c < nc ? min(8, rc - k) : 0;
+        if (left[u] == 8) {
+          gr[u] = load8u(g + o[u]);
+          mr[u] = load8u(m + o[u]);
+        }
+      }
+#pragma unroll
+      for (int u = 0; u < kUnalignedUnroll; ++u) {
+        if (left[u] == 8) {
+          float gf[8], mf[8];
+          unpack8(gr[u], gf);
+          unpack8(mr[u], mf);
+#pragma unroll
+          for (int i = 0; i < 8; ++i) mf[i] = fmaf(mu, mf[i], gf[i]);
+          store8u(m + o[u], mf);
+#pragma unroll
+          for (int i = 0; i < 8; ++i) {
+            const float mq = rt<TM>(mf[i]);
+            const float y = nesterov ? fmaf(mu, mq, gf[i]) : mq;
+            acc = fmaf(y, y, acc);
+          }
+        } else {
+          for (int i = 0; i < left[u]; ++i) {
+            const float gv = to_f<TG>(g[o[u] + i]);
+            const float mv = rt<TM>(fmaf(mu, to_f<TM>(m[o[u] + i]), gv));
+            m[o[u] + i] = from_f<TM>(mv);
+            const float y = nesterov ? fmaf(mu, mv, gv) : mv;
+            acc = fmaf(y, y, acc);
+          }
+        }
+      }
     }
   }
   acc = block_sum(acc);
@@ -271,8 +333,8 @@ __global__ __launch_bounds__(64) void k_scale(const ScaleDesc* __restrict__ sd,
 // problem, Y = M (or G + mu M with Nesterov).  The transposed copy goes
 // through LDS.  VEC: columns, windows and leading dimensions are multiples
 // of 8 elements and the pointers 16-byte aligned, so every access is one
-// 16-byte chunk of 8 elements (the last chunk of a Z^T row may be cut by the
-// problem's row count).
+// 16-byte chunk of 8 elements.  Rows of Z and Z^T are filled with zeros up to
+// a multiple of 8 elements: the GEMMs read their last chunk whole.
 // fuse_scale: s is computed here from the problem's partial sums, exactly
 // as k_scale computes it (same lanes, same order), instead of read from
 // scales (small problems: the separate launch costs more than the sum).
@@ -340,11 +402,7 @@ __global__ __launch_bounds__(kThreads) void k_pack(
 #pragma unroll
         for (int e = 0; e < 8; ++e) y[e] = tile[8 * j + e][cc];
         TN* p = dt + int64_t(c) * d.ld_t + r;
-        if (r + 8 <= d.rows) {
-          store8(p, y);
-        } else {
-          for (int e = 0; e < d.rows - r; ++e) gstore1(p + e, from_f<TN>(y[e]));
-        }
+        store8(p, y);  // zeros past the last row of Y
       }
     }
     return;
@@ -359,8 +417,8 @@ __global__ __launch_bounds__(kThreads) void k_pack(
       y = to_f<TM>(m[o]);
       if (nesterov) y = fmaf(mu, y, to_f<TG>(g[o]));
       y *= s;
-      if (ds) gstore1(ds + int64_t(r) * d.ld_s + c, from_f<TN>(y));
     }
+    if (ds && r < d.rows && c < ((d.cols + 7) & ~7)) gstore1(ds + int64_t(r) * d.ld_s + c, from_f<TN>(y));
     tile[lr + 4 * i][lc] = y;
   }
   if (!dt) return;  // uniform: no transposed copy wanted
@@ -368,7 +426,7 @@ __global__ __launch_bounds__(kThreads) void k_pack(
 #pragma unroll 4
   for (int i = 0; i < 16; ++i) {
     const int c = c0 + lr + 4 * i, r = r0 + lc;
-    if (r < d.rows && c < d.cols) gstore1(dt + int64_t(c) * d.ld_t + r, from_f<TN>(tile[lc][lr + 4 * i]));
+    if (r < ((d.rows + 7) & ~7) && c < d.cols) gstore1(dt + int64_t(c) * d.ld_t + r, from_f<TN>(tile[lc][lr + 4 * i]));
   }
 }
 
@@ -602,13 +660,17 @@ __device__ __forceinline__ float desc_alpha(const GemmDesc& d) {
 // Epilogue of the LDS-DMA kernel (bf16 C and Ct): the arithmetic of
 // gemm_epilogue in the same order (alpha acc, then + beta D, then + gamma
 // on the diagonal, one rounding to bf16), with the per-chunk work cut
-// down for tiles whose rows of C (and of Ct) are whole 8-element chunks:
+// down: rows of C (and of Ct) are written as whole 8-element chunks, by
 // buffer stores whose offset splits into a per-lane part fixed for the
 // tile and a wave-uniform part per pass, rows past the matrix sent past
 // the descriptor's byte count (the hardware drops them), the diagonal
 // term only on passes that cross the diagonal, and no workgroup barriers
 // (every wave stages in its own block, and the LDS runs one wave's
-// accesses in order).  Other tiles take gemm_epilogue.
+// accesses in order).  The last chunk of a row may reach past N (in Ct: past
+// M): leading dimensions are multiples of 8, so it ends inside the row's
+// padding, and what it writes there is zero (rows of X and Y past M and N
+// are read as zeros, and so is the padding of D).  The K loops rely on that:
+// they read their operands' last chunk whole.
 template <int TM, int TN, int WM, int WN>
 __device__ __forceinline__ void dma_epilogue(f32x16_t (&acc)[TM][TN], float* st, const GemmDesc& d, int m0,
                                              int n0, bool diag, float alpha) {
@@ -622,10 +684,6 @@ __device__ __forceinline__ void dma_epilogue(f32x16_t (&acc)[TM][TN], float* st,
   const bool mirror = d.Ct != nullptr && !diag;
   const bool has_d = d.D != nullptr;
   const float beta = d.beta, gamma = d.gamma;
-  if (d.N % 8 != 0 || (mirror && d.M % 8 != 0)) {
-    gemm_epilogue<bf16, TM, TN, WM, WN, false>(acc, st, d, m0, n0, diag, alpha, beta, gamma);
-    return;
-  }
   // Byte offsets as the sum of a per-lane part fixed for the tile (row and
   // column within the wave block) and a wave-uniform part per pass (the
   // block's origin).  A chunk outside the matrix takes the byte count
@@ -928,7 +986,8 @@ __global__ __launch_bounds__(kThreads * KS) void k_ns_gemm(const GemmDesc* __res
 
 // ---------------------------------------------------------------- NS GEMM, LDS-DMA staging
 //
-// The bf16 kernel below serves units whose K is a multiple of 8.  Operand
+// The bf16 kernels below read rows in chunks of 8 elements, the last one past
+// K into the row's zero padding (or K is a multiple of 8).  Operand
 // slices go straight from global memory into LDS (buffer_load_dwordx4 ...
 // lds: lane l of a wave writes 16 bytes at the wave's LDS window + 16 l),
 // through a ring of NS stages of 32-element (64-byte) K slices, NS - 1
@@ -1287,10 +1346,9 @@ __global__ __launch_bounds__(64 * WM * WN) void k_ns_gemm_dmap(const GemmDesc* _
   // diagonal, and the waves whose sub-tile lies strictly above it write
   // their block's transpose there (Ct = C): with 2 x 4 or 2 x 2 waves on a
   // square tile the blocks below are exactly the transposes of the blocks
-  // above.  (Not where the epilogue takes the general path: rows of C not
-  // whole 8-element chunks.)
+  // above.
   constexpr bool kDiagSkip = BM == BN && WM == 2 && (WN == 4 || WN == 2);
-  const bool dtile = kDiagSkip && ti == tj && d.sym && d.Ct == d.C && d.M % 8 == 0 && d.N % 8 == 0;
+  const bool dtile = kDiagSkip && ti == tj && d.sym && d.Ct == d.C;
   const int lr0 = wm * 32 * TM, lc0 = wn * 32 * TN;  // the wave's sub-tile inside the tile
   const bool below = dtile && lr0 >= lc0 + 32 * TN;
   const bool above = dtile && lc0 >= lr0 + 32 * TM;
@@ -2042,11 +2100,38 @@ __global__ __launch_bounds__(kThreads) void k_update(
       }
     }
   } else {
-    const int n = sd.nrows * cols;
-    for (int e = threadIdx.x; e < n; e += kThreads) {
-      const int r = e / cols, c = e - r * cols;
-      const int64_t ox = int64_t(r) * bd.ld + c;
-      x[ox] = from_f<TP>(fmaf(decay, to_f<TP>(x[ox]), -step * to_f<TU>(u[int64_t(r) * ud.ldu + c])));
+    // As in k_momentum; rows of U have their own pitch, so never flat.
+    const int cpr = (cols + 7) >> 3, nc = sd.nrows * cpr;
+    for (int c0 = threadIdx.x; c0 < nc; c0 += kThreads * kUnalignedUnroll) {
+      Raw8<TP> xr[kUnalignedUnroll];
+      Raw8<TU> ur[kUnalignedUnroll];
+      int64_t ox[kUnalignedUnroll], ou[kUnalignedUnroll];
+      int left[kUnalignedUnroll];
+#pragma unroll
+      for (int k = 0; k < kUnalignedUnroll; ++k) {
+        const int q = c0 + kThreads * k, r = q / cpr, c = (q - r * cpr) << 3;
+        ox[k] = int64_t(r) * bd.ld + c;
+        ou[k] = int64_t(r) * ud.ldu + c;
+        left[k] = q < nc ? min(8, cols - c) : 0;
+        if (left[k] == 8) {
+          xr[k] = load8u(x + ox[k]);
+          ur[k] = load8u(u + ou[k]);
+        }
+      }
+#pragma unroll
+      for (int k = 0; k < kUnalignedUnroll; ++k) {
+        if (left[k] == 8) {
+          float xf[8], uf[8];
+          unpack8(xr[k], xf);
+          unpack8(ur[k], uf);
+#pragma unroll
+          for (int i = 0; i < 8; ++i) xf[i] = fmaf(decay, xf[i], -step * uf[i]);
+          store8u(x + ox[k], xf);
+        } else {
+          for (int i = 0; i < left[k]; ++i)
+            x[ox[k] + i] = from_f<TP>(fmaf(decay, to_f<TP>(x[ox[k] + i]), -step * to_f<TU>(u[ou[k] + i])));
+        }
+      }
     }
   }
 }

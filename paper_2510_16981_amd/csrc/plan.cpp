@@ -227,8 +227,12 @@ std::vector<TileRef> xcd_order(const std::vector<TileRef>& logical) {
   return out;
 }
 
-bool dma_allowed(const std::vector<Problem>& probs, GemmKind kind, int ns_elem_bytes) {
+// padded: every kernel that writes an operand of this plan fills the rows'
+// last chunk of 8 elements with zeros (the pack and the DMA kernels' epilogues
+// do), so the DMA kernels may read it whole whatever K is.
+bool dma_allowed(const std::vector<Problem>& probs, GemmKind kind, int ns_elem_bytes, bool padded) {
   if (ns_elem_bytes != 2) return false;
+  if (padded) return true;
   for (const Problem& p : probs) {
     int64_t m, n, k;
     gemm_dims(p, kind, &m, &n, &k);
@@ -328,7 +332,9 @@ int32_t f32_split_variant(const std::vector<Problem>& probs, GemmKind kind) {
 int32_t choose_variant(const std::vector<Problem>& probs, GemmKind kind, int tile_policy,
                        int ns_elem_bytes, bool wave_k, bool lean) {
   const bool sym = kind != kApply;
-  const bool dma = dma_allowed(probs, kind, ns_elem_bytes);
+  // With the planner's own choice all three products run on DMA kernels; a
+  // forced shape keeps the register K loop where K is not a multiple of 8.
+  const bool dma = dma_allowed(probs, kind, ns_elem_bytes, tile_policy == 0 && !lean);
   if (tile_policy > 0) {
     int v = tile_policy - 1;
     // The block-ordered LDS-DMA loop these variants named was removed (the
@@ -349,7 +355,7 @@ int32_t choose_variant(const std::vector<Problem>& probs, GemmKind kind, int til
     }
     return v;
   }
-  // With the interleaved DMA loop (bf16, K a multiple of 8): the tile shape
+  // With the interleaved DMA loop (bf16): the tile shape
   // the time model above puts first (square shapes for the symmetric
   // products).  Register K loop otherwise (rules from per-launch
   // measurements on MI355X):
@@ -517,6 +523,7 @@ std::string build_layout(const MatrixShape* mats, int32_t n_mats,
   }
 
   const int64_t align_elems = kWsAlignBytes / ns_elem_bytes;
+  const bool padded = tile_policy == 0 && !lean;  // operands read in whole chunks (dma_allowed)
   for (int full = 0; full < 2; ++full) {
     Plan& plan = L.plan[full];
     plan.full = full != 0;
@@ -576,12 +583,13 @@ std::string build_layout(const MatrixShape* mats, int32_t n_mats,
       Problem& p = plan.probs[pi];
       p.gram = gram_mode != 1 && ns_elem_bytes == 2 && plan.nn_apply && ns_steps >= 2 &&
                (gram_mode == 2 || (p.S >= kGramMinS && 4 * p.L >= 5 * p.S));
-      // The momentum window as a GEMM operand: rows of 16-byte chunks (the
-      // arena is 16-byte aligned), within the kernels' 32-bit byte offsets.
+      // The momentum window as a GEMM operand: rows of whole 16-byte chunks
+      // (the arena is 16-byte aligned), within the kernels' 32-bit byte offsets.
       const MatrixShape& mm = mats[p.mat];
       const int64_t mom_off = L.mat_off[p.mat] + p.row0 * mm.cols + p.col0;
       p.in_place = in_place_input && ns_elem_bytes == 2 && ns_steps >= 1 && plan.nn_apply && !p.trans &&
-                   mm.cols % 8 == 0 && mom_off % 8 == 0 && p.rows * mm.cols * ns_elem_bytes < kMaxOperandBytes;
+                   mm.cols % 8 == 0 && (!padded || p.cols % 8 == 0) && mom_off % 8 == 0 &&
+                   p.rows * mm.cols * ns_elem_bytes < kMaxOperandBytes;
       if (!place_problem(&p, &cursor, align_elems, plan.nn_apply)) return "workspace too large";
       if (!p.in_place) add_pack_tiles(&plan, pi);
       plan.ns_flops += ns_unit_flops(p.S, p.L, ns_steps, p.gram);

@@ -173,7 +173,10 @@ struct Layout {
 // (Problem::in_place).
 // lean: the plan with the smallest tables and workspace, for callers whose
 // memory limit the faster one exceeds (none of the kernels only the planner
-// can choose: their smaller tiles have longer tile lists).
+// can choose: their smaller tiles have longer tile lists; bf16 units whose
+// sides are not multiples of 8 iterate as printed on the register K loop: the
+// Gram-space iteration's S x S buffers are more than the Z^T pair it keeps
+// below L = 1.5 S).
 std::string build_layout(const MatrixShape* mats, int32_t n_mats,
                          int ns_elem_bytes, int ns_steps, int poly_slots, int tile_policy,
                          int k_split, int apply_mode,
