@@ -108,7 +108,7 @@ constexpr bool gemm_reads_rows(int v) { return gemm_is_dmap(v) || v == kGemmWave
 // One workgroup tile of a grouped launch: problem index and packed
 // (tile row << 16 | tile column).
 struct TileRef {
-  int32_t prob;
+  int32_t prob;  // GEMM launches: -1 = an empty entry of the workgroup order
   int32_t ij;
   int32_t slot;  // K-split launches: index of the tile's partial sums and counter
   int32_t part;  // K-split launches: which share of the K slices

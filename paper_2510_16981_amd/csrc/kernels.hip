@@ -798,6 +798,7 @@ __global__ __launch_bounds__(kThreads * KS) void k_ns_gemm(const GemmDesc* __res
   __shared__ __attribute__((aligned(16))) unsigned char lds[G::LDS_BYTES];
 
   const TileRef t = tiles[blockIdx.x];
+  if (t.prob < 0) return;  // empty entry (balanced_order)
   const GemmDesc d = probs[t.prob];
   const float alpha = desc_alpha(d);
   const int ti = t.ij >> 16, tj = t.ij & 0xffff;
@@ -1172,6 +1173,7 @@ __global__ __launch_bounds__(64 * WM * WN) void k_ns_gemm_dmap(const GemmDesc* _
   __shared__ __attribute__((aligned(1024))) unsigned char lds[NS * G::STAGE > EPI ? NS * G::STAGE : EPI];
 
   const TileRef t = tiles[blockIdx.x];
+  if (t.prob < 0) return;  // empty entry (balanced_order)
   const GemmDesc d = probs[t.prob];
   const float alpha = desc_alpha(d);
   const int ti = t.ij >> 16, tj = t.ij & 0xffff;
@@ -1525,6 +1527,7 @@ __global__ __launch_bounds__(kThreads) void k_ns_gemm_wavek(const GemmDesc* __re
   static_assert(kRing <= kRed, "the sums reuse the rings");
   __shared__ __attribute__((aligned(1024))) unsigned char lds[kRed + 2 * T * T];
   const TileRef t = tiles[blockIdx.x];
+  if (t.prob < 0) return;  // empty entry (balanced_order)
   const GemmDesc d = probs[t.prob];
   const float alpha = desc_alpha(d);
   const int ti = t.ij >> 16, tj = t.ij & 0xffff;
@@ -1797,6 +1800,7 @@ __global__ __launch_bounds__(kThreads) void k_ns_gemm_f32(const GemmDesc* __rest
   static_assert(2 * STAGE >= EPI, "the epilogue stages in the slices' LDS");
   __shared__ __attribute__((aligned(16))) unsigned char lds[2 * STAGE];
   const TileRef t = tiles[blockIdx.x];
+  if (t.prob < 0) return;  // empty entry (balanced_order)
   const GemmDesc d = probs[t.prob];
   const float alpha = desc_alpha(d);
   const int ti = t.ij >> 16, tj = t.ij & 0xffff;
@@ -1960,6 +1964,7 @@ __global__ __launch_bounds__(kThreads) void k_ns_gemm_f32_wavek(const GemmDesc* 
   constexpr int T = 32, PD = 2, ES = 4, BK = 32;
   __shared__ __attribute__((aligned(16))) float red[4][16][64];
   const TileRef t = tiles[blockIdx.x];
+  if (t.prob < 0) return;  // empty entry (balanced_order)
   const GemmDesc d = probs[t.prob];
   const float alpha = desc_alpha(d);
   const int ti = t.ij >> 16, tj = t.ij & 0xffff;

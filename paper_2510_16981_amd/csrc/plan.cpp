@@ -4,6 +4,7 @@
 #include "plan.h"
 
 #include <algorithm>
+#include <iterator>
 #include <limits>
 #include <utility>
 
@@ -125,6 +126,82 @@ int32_t first_apply_slot(const Problem& p, int ns_steps) {
 
 namespace {
 
+// One unit's tiles in a launch's logical order, and their K slices.
+struct UnitTiles {
+  int64_t begin, end, slices;
+};
+
+// Workgroup order of a launch with more tiles than CUs.  Each XCD's share is
+// the same work instead of the same number of tiles (a tile of a 4096-wide
+// matrix's shard takes four times as long as one of a 1024-wide one's): of
+// the units of one shape each XCD takes as many as every other, the rest is
+// handed out tile by tile where least is.  A share is walked longest tiles
+// first, so that no long one is left for the end, and its units in reverse
+// where `reverse` is set: a launch then starts on what the one before it left
+// in the last-level cache.  Workgroup w runs on XCD w % 8: shorter shares are
+// filled up with empty entries (prob = -1), which the kernels skip.  Measured
+// against equal runs of tiles in problem order (us): Gram of the 1024 x 7168
+// and 3584 x 2048 shards of two MLP matrices 367 -> 281 and their apply 490 ->
+// 428; apply of one layer of the 8B-shaped model's block step 732 -> 626, Gram
+// of its full step 2705 -> 2046; 8192 x 256 next to 2048 x 1024 shards, Gram
+// 1000 -> 794; the reversal alone 0.3-2.3% of a step.
+std::vector<TileRef> balanced_order(const std::vector<TileRef>& logical, std::vector<UnitTiles> units, bool reverse) {
+  constexpr int64_t kFixed = 14;  // a tile's prologue and epilogue, in K slices
+  auto longer = [](const UnitTiles& a, const UnitTiles& b) { return a.slices > b.slices; };
+  std::stable_sort(units.begin(), units.end(), longer);
+  std::vector<UnitTiles> share[kNumXCDs], rest;
+  int64_t load[kNumXCDs] = {}, total = 0;
+  auto weight = [](const UnitTiles& u) { return (u.end - u.begin) * (u.slices + kFixed); };
+  for (size_t i = 0; i < units.size();) {
+    size_t j = i;
+    while (j < units.size() && units[j].slices == units[i].slices &&
+           units[j].end - units[j].begin == units[i].end - units[i].begin)
+      ++j;
+    const size_t each = (j - i) / kNumXCDs;
+    for (size_t k = i; k < j; ++k) {
+      total += weight(units[k]);
+      const size_t x = each > 0 ? (k - i) / each : size_t(kNumXCDs);
+      if (x < size_t(kNumXCDs)) {
+        share[x].push_back(units[k]);
+        load[x] += weight(units[k]);
+      } else {
+        rest.push_back(units[k]);
+      }
+    }
+    i = j;
+  }
+  // The rest: the least loaded XCD takes tiles up to the mean.
+  const int64_t mean = (total + kNumXCDs - 1) / kNumXCDs;
+  for (UnitTiles u : rest)
+    while (u.begin < u.end) {
+      const int x = int(std::min_element(load, load + kNumXCDs) - load);
+      const int64_t per = u.slices + kFixed;
+      const int64_t n = std::min(u.end - u.begin, std::max<int64_t>(1, (mean - load[x] + per - 1) / per));
+      share[x].push_back(UnitTiles{u.begin, u.begin + n, u.slices});
+      load[x] += n * per;
+      u.begin += n;
+    }
+  int64_t most = 0;
+  std::vector<TileRef> run[kNumXCDs];
+  for (int x = 0; x < kNumXCDs; ++x) {
+    if (reverse) std::reverse(share[x].begin(), share[x].end());
+    std::stable_sort(share[x].begin(), share[x].end(), longer);
+    for (const UnitTiles& u : share[x]) {
+      const auto b = logical.begin() + u.begin, e = logical.begin() + u.end;
+      if (reverse)
+        run[x].insert(run[x].end(), std::make_reverse_iterator(e), std::make_reverse_iterator(b));
+      else
+        run[x].insert(run[x].end(), b, e);
+    }
+    most = std::max(most, int64_t(run[x].size()));
+  }
+  std::vector<TileRef> out(size_t(most * kNumXCDs), TileRef{-1, 0, 0, 0});
+  for (int x = 0; x < kNumXCDs; ++x)
+    for (size_t j = 0; j < run[x].size(); ++j) out[j * kNumXCDs + x] = run[x][j];
+  while (!out.empty() && out.back().prob < 0) out.pop_back();
+  return out;
+}
+
 int32_t slot_of(GemmKind kind, int iter, int ns_steps, int poly_slots) {
   const int q = iter & 1;
   return kind == kGram   ? kSlotGram0 + q
@@ -141,13 +218,14 @@ int32_t slot_of(GemmKind kind, int iter, int ns_steps, int poly_slots) {
 // the apply (every unit that iterates as printed; a Gram-space unit's Z <-
 // Q Z at the end of each segment).  The Gram-space products take the
 // polynomial's tile shape (all are S x S x S).
-void build_phases(Plan* plan, int ns_steps, int poly_slots, int desc_per_problem, int ns_elem_bytes) {
+void build_phases(Plan* plan, int ns_steps, int poly_slots, int desc_per_problem, int ns_elem_bytes, bool lean) {
   plan->phases.clear();
   plan->split_floats = plan->split_slots = 0;
   const int32_t np = int32_t(plan->probs.size());
   using Item = std::pair<int32_t, int32_t>;  // (problem, descriptor slot)
   auto add_phase = [&](GemmKind kind, const std::vector<Item>& items) {
     if (items.empty()) return;
+    std::vector<UnitTiles> units;
     GemmPhase phase;
     phase.variant = plan->variant[kind];
     phase.kind = kind;
@@ -161,7 +239,11 @@ void build_phases(Plan* plan, int ns_steps, int poly_slots, int desc_per_problem
         gemm_dims(p, kind, &m, &n, &k);
         phase.long_k = phase.long_k || k > kLongK;
       }
+      const int64_t t0 = int64_t(logical.size());
       append_tiles(p, kind, phase.variant, it.first * desc_per_problem + it.second, &logical);
+      int64_t m, n, k;
+      gemm_dims(p, kind, &m, &n, &k);
+      units.push_back(UnitTiles{t0, int64_t(logical.size()), ceil_div(k, 32)});
     }
     if (phase.nsplit > 1) {
       // The shares of one tile are adjacent, so that the XCD order below
@@ -177,7 +259,12 @@ void build_phases(Plan* plan, int ns_steps, int poly_slots, int desc_per_problem
                                   kGemmTileRows[phase.variant] * kGemmTileCols[phase.variant]);
       logical.swap(parts);
     }
-    phase.tiles = xcd_order(logical);
+    // A launch of several rounds: the XCDs' shares balanced, and the units
+    // walked the other way round in every second launch.
+    if (!lean && phase.nsplit == 1 && int64_t(logical.size()) > kNumCUs)
+      phase.tiles = balanced_order(logical, std::move(units), plan->phases.size() % 2 == 1);
+    else
+      phase.tiles = xcd_order(logical);
     plan->phases.push_back(std::move(phase));
   };
   for (int iter = 0; iter < ns_steps; ++iter) {
@@ -596,7 +683,7 @@ std::string build_layout(const MatrixShape* mats, int32_t n_mats,
       plan.ns_dense_flops += ns_unit_dense_flops(p.S, p.L, ns_steps);
     }
     plan.ws_elems = cursor;
-    build_phases(&plan, ns_steps, poly_slots, L.desc_per_problem, ns_elem_bytes);
+    build_phases(&plan, ns_steps, poly_slots, L.desc_per_problem, ns_elem_bytes, lean);
     if (plan.pack_tiles.size() > size_t(std::numeric_limits<int32_t>::max() / 2))
       return "too many tiles";
   }
