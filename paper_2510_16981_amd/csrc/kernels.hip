@@ -316,15 +316,28 @@ __global__ __launch_bounds__(kThreads) void k_check_finite(const float* __restri
 
 // ---------------------------------------------------------------- scale
 
+// 1 / (||Y||_F + eps) of a unit from its partial sums, by one wave (valid in
+// lane 0); eight loads in flight, added in one order whatever their number.
+__device__ __forceinline__ float unit_scale(const float* __restrict__ partials, int begin, int end, float eps) {
+  double acc = 0.0;
+  for (int i = begin + int(threadIdx.x); i < end; i += 64 * 8) {
+    float v[8];
+#pragma unroll
+    for (int k = 0; k < 8; ++k) v[k] = i + 64 * k < end ? partials[i + 64 * k] : 0.f;
+#pragma unroll
+    for (int k = 0; k < 8; ++k) acc += v[k];
+  }
+#pragma unroll
+  for (int o = 32; o > 0; o >>= 1) acc += __shfl_xor(acc, o);
+  return float(1.0 / (sqrt(acc) + double(eps)));
+}
+
 __global__ __launch_bounds__(64) void k_scale(const ScaleDesc* __restrict__ sd,
                                               const float* __restrict__ partials,
                                               float* __restrict__ scales, float eps) {
   const ScaleDesc d = sd[blockIdx.x];
-  double acc = 0.0;
-  for (int i = d.seg_begin + int(threadIdx.x); i < d.seg_end; i += 64) acc += partials[i];
-#pragma unroll
-  for (int o = 32; o > 0; o >>= 1) acc += __shfl_xor(acc, o);
-  if (threadIdx.x == 0) scales[blockIdx.x] = float(1.0 / (sqrt(acc) + double(eps)));
+  const float s = unit_scale(partials, d.seg_begin, d.seg_end, eps);
+  if (threadIdx.x == 0) scales[blockIdx.x] = s;
 }
 
 // ---------------------------------------------------------------- pack
@@ -351,11 +364,8 @@ __global__ __launch_bounds__(kThreads) void k_pack(
   const int r0 = (t.ij >> 16) * 64, c0 = (t.ij & 0xffff) * 64;
   if (fuse_scale) {  // uniform
     if (threadIdx.x < 64) {
-      double acc = 0.0;
-      for (int i = d.seg_begin + int(threadIdx.x); i < d.seg_end; i += 64) acc += partials[i];
-#pragma unroll
-      for (int o = 32; o > 0; o >>= 1) acc += __shfl_xor(acc, o);
-      if (threadIdx.x == 0) s_fused = float(1.0 / (sqrt(acc) + double(eps)));
+      const float sc = unit_scale(partials, d.seg_begin, d.seg_end, eps);
+      if (threadIdx.x == 0) s_fused = sc;
     }
     __syncthreads();
   }

@@ -567,11 +567,25 @@ std::string build_layout(const MatrixShape* mats, int32_t n_mats,
   L.poly_slots = poly_slots;
   L.desc_per_problem = kSlotPoly0 + 2 * poly_slots;
 
+  // Elements per segment: kSegTarget, or fewer (at least 2048, one 16-byte
+  // chunk of bf16 per thread) where that many would leave CUs without a
+  // workgroup; with windows off the 16-byte grid, whose chunks go four at a
+  // time with more index work each, where they leave fewer than four per CU
+  // (3.2 M elements in odd windows: momentum 17.8 -> 10.4 us, update 17.3 ->
+  // 8.8).  Aligned windows gain nothing beyond one workgroup per CU, and every
+  // segment is one more term of its unit's scale (12.6 M elements in twice the
+  // segments: k_scale 8.0 -> 10.7 us).
+  bool aligned = true;
+  for (const MatrixShape& m : L.mats) aligned = aligned && m.cols % m.grid_cols == 0 && m.cols / m.grid_cols % 8 == 0;
+  const int64_t least = (aligned ? 1 : 4) * kNumCUs;
+  int64_t seg_target = kSegTarget;
+  while (!lean && seg_target > 2048 && elems / seg_target < least) seg_target /= 2;
+
   // Blocks in matrix order, row-major inside each grid; segments per block.
   for (int32_t k = 0; k < n_mats; ++k) {
     const MatrixShape& m = mats[k];
     const int64_t br = m.rows / m.grid_rows, bc = m.cols / m.grid_cols;
-    const int64_t rows_per_seg = std::max<int64_t>(1, std::min(br, kSegTarget / bc));
+    const int64_t rows_per_seg = std::max<int64_t>(1, std::min(br, seg_target / bc));
     for (int32_t i = 0; i < m.grid_rows; ++i)
       for (int32_t j = 0; j < m.grid_cols; ++j) {
         BlockPlan b{k, i * br, j * bc, br, bc, int32_t(L.segs.size()), 0};
@@ -665,11 +679,12 @@ std::string build_layout(const MatrixShape* mats, int32_t n_mats,
         return "too many tiles";
     }
     plan.nn_apply = apply_mode == 0 && gemm_reads_rows(plan.variant[kApply]);
+    for (Problem& p : plan.probs)
+      p.gram = gram_mode != 1 && ns_elem_bytes == 2 && plan.nn_apply && ns_steps >= 2 &&
+               (gram_mode == 2 || (p.S >= kGramMinS && 4 * p.L >= 5 * p.S));
     int64_t cursor = 0;
     for (int32_t pi = 0; pi < int32_t(plan.probs.size()); ++pi) {
       Problem& p = plan.probs[pi];
-      p.gram = gram_mode != 1 && ns_elem_bytes == 2 && plan.nn_apply && ns_steps >= 2 &&
-               (gram_mode == 2 || (p.S >= kGramMinS && 4 * p.L >= 5 * p.S));
       // The momentum window as a GEMM operand: rows of whole 16-byte chunks
       // (the arena is 16-byte aligned), within the kernels' 32-bit byte offsets.
       const MatrixShape& mm = mats[p.mat];
