@@ -56,6 +56,37 @@ bool place_problem(Problem* p, int64_t* cursor, int64_t align_elems, bool nn) {
   return *cursor > 0 && *cursor < (int64_t(1) << 46);
 }
 
+// A plan of both kinds of iteration has a Gram and an apply launch for every
+// iteration (its units as printed) on top of the Gram-space products: 23
+// launches for K = 5, against 17 where every unit runs the Gram-space
+// iteration.  Down to L = S that is no more flops (20 S^3 either way), only
+// more of them in the slower products, so where the launches saved are worth
+// more than that, the remaining units follow: none below kGramMinS, and none
+// above 512 rows, whose launches take several times their fixed cost.  A launch
+// of a small plan costs 4-5 us; rates as for kGramMinS, halved (launches of
+// few tiles).  The block step of one layer of width 512: 210 -> 188 us.
+void unify_iteration(std::vector<Problem>* probs, int ns_steps) {
+  double extra_us = 0;
+  bool some = false, all = true;
+  for (const Problem& p : *probs) {
+    if (p.gram) {
+      some = true;
+      continue;
+    }
+    all = false;
+    if (p.S < kGramMinS || p.S > 512) return;
+    const double s = double(p.S), l = double(p.L), gram = s * s * l / 550e6, sym = s * s * s / 445e6,
+                 apply = 2 * s * s * l / 495e6;
+    double in_gram = 0;
+    for (int k0 = 0; k0 < ns_steps; k0 += kGramSegment)
+      in_gram += gram + (4.0 * std::min(kGramSegment, ns_steps - k0) - 3.0) * sym + apply;
+    extra_us += in_gram - ns_steps * (gram + sym + apply);
+  }
+  const int segments = (ns_steps + kGramSegment - 1) / kGramSegment;
+  if (!some || all || extra_us > 2 * (ns_steps - segments) * 4.0) return;
+  for (Problem& p : *probs) p.gram = true;
+}
+
 // Largest operand of a problem in bytes (Z in either layout, A, B).
 int64_t max_operand_bytes(const Problem& p, int es) {
   return std::max(std::max(p.S * p.Lp, p.L * p.Sp), p.S * p.Sp) * int64_t(es);
@@ -682,6 +713,7 @@ std::string build_layout(const MatrixShape* mats, int32_t n_mats,
     for (Problem& p : plan.probs)
       p.gram = gram_mode != 1 && ns_elem_bytes == 2 && plan.nn_apply && ns_steps >= 2 &&
                (gram_mode == 2 || (p.S >= kGramMinS && 4 * p.L >= 5 * p.S));
+    if (gram_mode == 0 && padded) unify_iteration(&plan.probs, ns_steps);
     int64_t cursor = 0;
     for (int32_t pi = 0; pi < int32_t(plan.probs.size()); ++pi) {
       Problem& p = plan.probs[pi];
