@@ -59,7 +59,9 @@ bool place_problem(Problem* p, int64_t* cursor, int64_t align_elems, bool nn) {
 // A plan of both kinds of iteration has a Gram and an apply launch for every
 // iteration (its units as printed) on top of the Gram-space products: 23
 // launches for K = 5, against 17 where every unit runs the Gram-space
-// iteration.  Down to L = S that is no more flops (20 S^3 either way), only
+// iteration (with the paper's quintic its U is 0.67 to 0.89 times as far from
+// 64 bits as printed, at ten sizes from 129 x 1000 to 999 x 1333 with gradients
+// of rank 4 to 128, L = S among them).  Down to L = S that is no more flops (20 S^3 either way), only
 // more of them in the slower products, so where the launches saved are worth
 // more than that, the remaining units follow: none below kGramMinS, and none
 // above 512 rows, whose launches take several times their fixed cost.  A launch
@@ -567,7 +569,7 @@ double ns_unit_dense_flops(int64_t S, int64_t L, int K) {
 std::string build_layout(const MatrixShape* mats, int32_t n_mats,
                          int ns_elem_bytes, int ns_steps, int poly_slots, int tile_policy,
                          int k_split, int apply_mode, Layout* out, bool* shape_error, int gram_mode,
-                         bool in_place_input, bool lean) {
+                         bool in_place_input, bool lean, bool quintic) {
   *shape_error = false;
   if (!mats || n_mats <= 0) return "mats must be a non-empty array";
   if (ns_steps < 0) return "ns_steps must be >= 0";
@@ -710,10 +712,17 @@ std::string build_layout(const MatrixShape* mats, int32_t n_mats,
         return "too many tiles";
     }
     plan.nn_apply = apply_mode == 0 && gemm_reads_rows(plan.variant[kApply]);
+    // Steeper polynomials than the paper's quintic lose precision in Gram
+    // space (U of 129 x 1000 with a = 3.44 in two iterations: 0.87% from 64
+    // bits as printed, 2.7% in Gram space; with the quintic 0.95% and 0.73%):
+    // with other coefficients only the plans that have always run it do,
+    // those whose units' smaller sides are all multiples of 8.
+    bool chunks = true;
+    for (const Problem& p : plan.probs) chunks = chunks && p.S % 8 == 0;
     for (Problem& p : plan.probs)
       p.gram = gram_mode != 1 && ns_elem_bytes == 2 && plan.nn_apply && ns_steps >= 2 &&
-               (gram_mode == 2 || (p.S >= kGramMinS && 4 * p.L >= 5 * p.S));
-    if (gram_mode == 0 && padded) unify_iteration(&plan.probs, ns_steps);
+               (quintic || chunks) && (gram_mode == 2 || (p.S >= kGramMinS && 4 * p.L >= 5 * p.S));
+    if (gram_mode == 0 && padded && quintic) unify_iteration(&plan.probs, ns_steps);
     int64_t cursor = 0;
     for (int32_t pi = 0; pi < int32_t(plan.probs.size()); ++pi) {
       Problem& p = plan.probs[pi];

@@ -74,9 +74,15 @@ std::string layout_for(const std::vector<MatrixShape>& shapes, const muonbp_opti
   // and no Nesterov blend is formed.
   const bool in_place = momentum_aligned && o.state_dtype == MUONBP_BF16 && o.ns_dtype == MUONBP_BF16 &&
                         o.nesterov == 0;
+  bool quintic = true;
+  for (int k = 0; k < o.ns_steps; ++k) {
+    float a, b, c;
+    ns_coeffs(o, k, &a, &b, &c);
+    quintic = quintic && a == 2.0f && b == -1.5f && c == 0.5f;
+  }
   return build_layout(shapes.data(), int32_t(shapes.size()), int(dtype_size(o.ns_dtype)), o.ns_steps,
                       poly_slots(o), o.tile_policy, o.k_split, o.apply_mode, out, shape_error,
-                      o.gram_iteration, in_place, lean);
+                      o.gram_iteration, in_place, lean, quintic);
 }
 
 void build_plan_host_tables(const Layout& lay, const muonbp_options& o, int full, void* ws_base,

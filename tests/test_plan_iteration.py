@@ -36,3 +36,14 @@ def test_options_still_decide():
     # A forced tile shape keeps the flop rule; one iteration has no Gram-space form.
     assert mb.describe_plan(mats, True, mb.options_default(tile_policy=8)).gram_units == 1
     assert mb.describe_plan(mats, True, mb.options_default(ns_steps=1)).gram_units == 0
+
+
+def test_other_coefficients_keep_the_flop_rule():
+    """Beyond the paper's quintic, only what ran in Gram space before does."""
+    steep = dict(coeffs=[(3.4445, -4.7750, 2.0315), (2.0, -1.5, 0.5)])
+    odd = (129, 1000, 1, 1)
+    assert mb.describe_plan([WIDE, SQUARE], True, mb.options_default(**steep)).gram_units == 1
+    assert mb.describe_plan([odd], True).gram_units == 1
+    assert mb.describe_plan([odd], True, mb.options_default(**steep)).gram_units == 0
+    assert mb.describe_plan([WIDE, odd], True, mb.options_default(a=3.0)).gram_units == 0
+    assert mb.describe_plan([odd], True, mb.options_default(coeffs=[(2.0, -1.5, 0.5)] * 3)).gram_units == 1
