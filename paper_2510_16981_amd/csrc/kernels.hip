@@ -1447,17 +1447,91 @@ __global__ __launch_bounds__(64 * WM * WN) void k_ns_gemm_dmap(const GemmDesc* _
       frag_wait(f0, y0l, y0h);
     }
   };
+  // 128 x 128 tiles: a wave's 8 MFMAs of a slice are too few to hide the reads
+  // one K step ahead at one wave per SIMD (630-690 clocks a slice for 256 of
+  // MFMA), and its 64 accumulators leave registers for both K steps of two
+  // slices.  So both steps of slice kt + 1 are read under the MFMAs of slice
+  // kt, behind one barrier: 515 clocks, 2048 x 768 shards' step 302 -> 296 us,
+  // whole 2048 x 6144 539 -> 530.  (Two slices per barrier in eight slots, one
+  // workgroup per CU, were slower than the plain loop, 306 us; on 256 x 256
+  // tiles the registers do not suffice for 4 waves and 8 waves gain nothing.)
+  constexpr bool kAhead = W == 4 && BM == 128 && BN == 128;
+  auto kloop_ahead = [&](auto math, auto sh) {
+    constexpr bool MATH = decltype(math)::value;
+    constexpr int LP = decltype(sh)::value ? XG / W : LPW;
+    constexpr int MF = 2 * NM, RD = 2 * NR;
+    Fr fr[2][2];
+    Yh yl[2][2], yh[2][2];
+    auto rd = [&](auto set, int kt, int o) {
+      constexpr int P = decltype(set)::value;
+      read_op(sh, fr[P][o / NR], yl[P][o / NR], yh[P][o / NR], kt, o / NR, o % NR);
+    };
+    auto wait_all = [&](auto set) {
+      constexpr int P = decltype(set)::value;
+#pragma unroll
+      for (int st = 0; st < 2; ++st) frag_wait(fr[P][st], yl[P][st], yh[P][st]);
+    };
+#pragma unroll
+    for (int s = 0; s < NS; ++s)
+#pragma unroll
+      for (int jj = 0; jj < LP; ++jj) copy(kb + s, jj);
+    __builtin_amdgcn_s_waitcnt(vmcnt_imm((NS - 1) * LP));
+    barrier_no_fence();
+    if constexpr (MATH) {
+#pragma unroll
+      for (int o = 0; o < RD; ++o) rd(std::integral_constant<int, 0>{}, kb, o);
+      wait_all(std::integral_constant<int, 0>{});
+    }
+    // Slice kt from register set P.
+    auto slice = [&](auto set, auto other, int kt) {
+      constexpr int P = decltype(set)::value;
+#pragma unroll
+      for (int q = 0; q < H; ++q) {
+        if constexpr (MATH) mfma(fr[P][q / NM], q % NM);
+        __builtin_amdgcn_sched_barrier(0);
+      }
+      // Slice kt + 1 has landed for this wave (two later ones may be in
+      // flight), after the barrier for every wave; every wave holds slice kt in
+      // registers, so its slot takes slice kt + NS.
+      __builtin_amdgcn_s_waitcnt(vmcnt_imm((NS - 2) * LP));
+      barrier_no_fence();
+      constexpr int R = MF - H, RR = R - 3;  // the last MFMAs hide the last reads
+#pragma unroll
+      for (int q = H; q < MF; ++q) {
+        const int i = q - H;
+        if constexpr (MATH) {
+          mfma(fr[P][q / NM], q % NM);
+#pragma unroll
+          for (int o = i * RD / RR; o < (i + 1) * RD / RR && o < RD; ++o) rd(other, kt + 1, o);
+        }
+#pragma unroll
+        for (int o = i * LP / R; o < (i + 1) * LP / R; ++o) copy(kt + NS, o);
+        __builtin_amdgcn_sched_barrier(0);
+      }
+      if constexpr (MATH) wait_all(other);
+    };
+    for (int kt = kb; kt < ke; kt += 2) {
+      slice(std::integral_constant<int, 0>{}, std::integral_constant<int, 1>{}, kt);
+      if (kt + 1 < ke) slice(std::integral_constant<int, 1>{}, std::integral_constant<int, 0>{}, kt + 1);
+    }
+  };
+  auto loop = [&](auto math, auto sh) {
+    if constexpr (kAhead)
+      kloop_ahead(math, sh);
+    else
+      kloop(math, sh);
+  };
   if (share_xy) {
     if constexpr (kShareXY) {
       if (idle)
-        kloop(std::false_type{}, std::true_type{});
+        loop(std::false_type{}, std::true_type{});
       else
-        kloop(std::true_type{}, std::true_type{});
+        loop(std::true_type{}, std::true_type{});
     }
   } else if (idle) {
-    kloop(std::false_type{}, std::false_type{});
+    loop(std::false_type{}, std::false_type{});
   } else {
-    kloop(std::true_type{}, std::false_type{});
+    loop(std::true_type{}, std::false_type{});
   }
   // Zero-filled copies past the share may still be in flight: let them land
   // before the epilogue reuses the ring.
