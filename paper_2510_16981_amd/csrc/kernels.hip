@@ -344,10 +344,13 @@ __global__ __launch_bounds__(64) void k_scale(const ScaleDesc* __restrict__ sd,
 
 // Z = s Y (straight) and Z^T = s Y^T (transposed) for one 64 x 64 tile of a
 // problem, Y = M (or G + mu M with Nesterov).  The transposed copy goes
-// through LDS.  VEC: columns, windows and leading dimensions are multiples
-// of 8 elements and the pointers 16-byte aligned, so every access is one
-// 16-byte chunk of 8 elements.  Rows of Z and Z^T are filled with zeros up to
-// a multiple of 8 elements: the GEMMs read their last chunk whole.
+// through LDS.  Rows of Z and Z^T start on 16-byte boundaries and are filled
+// with zeros up to a multiple of 8 elements, which the GEMMs' last chunks read,
+// so every store is a whole 16-byte chunk.  VEC: so is every load (columns,
+// windows and leading dimensions are multiples of 8 elements and the pointers
+// 16-byte aligned); otherwise chunks are read at whatever address they have, a
+// row's last partial one element by element (3.2 M elements in odd windows: 12.4
+// us, 15.7 element by element).
 // fuse_scale: s is computed here from the problem's partial sums, exactly
 // as k_scale computes it (same lanes, same order), instead of read from
 // scales (small problems: the separate launch costs more than the sum).
@@ -374,69 +377,58 @@ __global__ __launch_bounds__(kThreads) void k_pack(
   const TG* g = static_cast<const TG*>(mats[d.mat].grad) + d.in_mat_off;
   TN* ds = static_cast<TN*>(d.dst_s);
   TN* dt = static_cast<TN*>(d.dst_t);
-  if (VEC) {
-    // Straight copy: 64 rows x 8 chunks, two chunks per thread.
+  // Eight elements of a row at column c, zeros past the last one.
+  auto load_row = [&](const auto* q, int c, float f[8]) {
+    using E = std::remove_const_t<std::remove_pointer_t<decltype(q)>>;
+    if constexpr (VEC) {
+      load8(q, f);
+    } else if (c + 8 <= d.cols) {
+      const Raw8<E> w = load8u(q);
+      unpack8(w, f);
+    } else {
 #pragma unroll
-    for (int i = 0; i < 2; ++i) {
-      const int q = threadIdx.x + kThreads * i, rr = q >> 3, ch = q & 7;
-      const int r = r0 + rr, c = c0 + 8 * ch;
-      float y[8];
-      if (r < d.rows && c < d.cols) {
-        const int64_t o = int64_t(r) * d.ld + c;
-        load8(m + o, y);
-        if (nesterov) {
-          float gv[8];
-          load8(g + o, gv);
-#pragma unroll
-          for (int e = 0; e < 8; ++e) y[e] = fmaf(mu, y[e], gv[e]);
-        }
-#pragma unroll
-        for (int e = 0; e < 8; ++e) y[e] *= s;
-        if (ds) store8(ds + int64_t(r) * d.ld_s + c, y);
-      } else {
-#pragma unroll
-        for (int e = 0; e < 8; ++e) y[e] = 0.f;
-      }
-#pragma unroll
-      for (int e = 0; e < 8; ++e) tile[rr][8 * ch + e] = y[e];
+      for (int e = 0; e < 8; ++e) f[e] = c + e < d.cols ? to_f<E>(q[e]) : 0.f;
     }
-    if (!dt) return;  // uniform: no transposed copy wanted
-    __syncthreads();
-    // Transposed copy: Z^T rows c0 .. c0 + 63, chunks of 8 rows of Y.
+  };
+  // Straight copy: 64 rows x 8 chunks, two chunks per thread.
 #pragma unroll
-    for (int i = 0; i < 2; ++i) {
-      const int q = threadIdx.x + kThreads * i, cc = q >> 3, j = q & 7;
-      const int c = c0 + cc, r = r0 + 8 * j;
-      if (c < d.cols && r < d.rows) {
-        float y[8];
-#pragma unroll
-        for (int e = 0; e < 8; ++e) y[e] = tile[8 * j + e][cc];
-        TN* p = dt + int64_t(c) * d.ld_t + r;
-        store8(p, y);  // zeros past the last row of Y
-      }
-    }
-    return;
-  }
-  const int lc = threadIdx.x & 63, lr = threadIdx.x >> 6;
-#pragma unroll 4
-  for (int i = 0; i < 16; ++i) {
-    const int r = r0 + lr + 4 * i, c = c0 + lc;
-    float y = 0.f;
+  for (int i = 0; i < 2; ++i) {
+    const int q = threadIdx.x + kThreads * i, rr = q >> 3, ch = q & 7;
+    const int r = r0 + rr, c = c0 + 8 * ch;
+    float y[8];
     if (r < d.rows && c < d.cols) {
       const int64_t o = int64_t(r) * d.ld + c;
-      y = to_f<TM>(m[o]);
-      if (nesterov) y = fmaf(mu, y, to_f<TG>(g[o]));
-      y *= s;
+      load_row(m + o, c, y);
+      if (nesterov) {
+        float gv[8];
+        load_row(g + o, c, gv);
+#pragma unroll
+        for (int e = 0; e < 8; ++e) y[e] = fmaf(mu, y[e], gv[e]);
+      }
+#pragma unroll
+      for (int e = 0; e < 8; ++e) y[e] = VEC || c + e < d.cols ? y[e] * s : 0.f;  // s may be infinite
+      if (ds) store8(ds + int64_t(r) * d.ld_s + c, y);
+    } else {
+#pragma unroll
+      for (int e = 0; e < 8; ++e) y[e] = 0.f;
     }
-    if (ds && r < d.rows && c < ((d.cols + 7) & ~7)) gstore1(ds + int64_t(r) * d.ld_s + c, from_f<TN>(y));
-    tile[lr + 4 * i][lc] = y;
+#pragma unroll
+    for (int e = 0; e < 8; ++e) tile[rr][8 * ch + e] = y[e];
   }
   if (!dt) return;  // uniform: no transposed copy wanted
   __syncthreads();
-#pragma unroll 4
-  for (int i = 0; i < 16; ++i) {
-    const int c = c0 + lr + 4 * i, r = r0 + lc;
-    if (r < ((d.rows + 7) & ~7) && c < d.cols) gstore1(dt + int64_t(c) * d.ld_t + r, from_f<TN>(tile[lc][lr + 4 * i]));
+  // Transposed copy: Z^T rows c0 .. c0 + 63, chunks of 8 rows of Y (zeros past
+  // the last one).
+#pragma unroll
+  for (int i = 0; i < 2; ++i) {
+    const int q = threadIdx.x + kThreads * i, cc = q >> 3, j = q & 7;
+    const int c = c0 + cc, r = r0 + 8 * j;
+    if (c < d.cols && r < d.rows) {
+      float y[8];
+#pragma unroll
+      for (int e = 0; e < 8; ++e) y[e] = tile[8 * j + e][cc];
+      store8(dt + int64_t(c) * d.ld_t + r, y);
+    }
   }
 }
 
