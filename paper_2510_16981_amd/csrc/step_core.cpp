@@ -3,6 +3,7 @@
 
 #include <algorithm>
 #include <cmath>
+#include <utility>
 
 namespace muonbp {
 
@@ -307,12 +308,20 @@ ScratchPlan scratch_plan(const Layout& lay, int full, const muonbp_options& o) {
 
 std::string scratch_layout(const std::vector<MatrixShape>& shapes, const muonbp_options& o, int full,
                            int64_t limit, bool momentum_aligned, Layout* lay, ScratchPlan* sp, bool* shape_error) {
-  std::string msg;
-  for (const bool lean : {false, true}) {
-    msg = layout_for(shapes, o, lay, shape_error, momentum_aligned, lean);
-    if (!msg.empty()) return msg;
-    *sp = scratch_plan(*lay, full, o);
-    if (sp->total <= limit) break;
+  std::string msg = layout_for(shapes, o, lay, shape_error, momentum_aligned, false);
+  if (!msg.empty()) return msg;
+  *sp = scratch_plan(*lay, full, o);
+  // The lean form is less than three times as large (Z and Z^T twice instead of
+  // Z twice, and the sums of a K split), so it need not be asked below a third
+  // of the limit.
+  if (3 * sp->total <= limit) return msg;
+  Layout lean;
+  msg = layout_for(shapes, o, &lean, shape_error, momentum_aligned, true);
+  if (!msg.empty()) return msg;
+  const ScratchPlan lean_sp = scratch_plan(lean, full, o);
+  if (lean_sp.total > limit || sp->total > limit) {
+    *lay = std::move(lean);
+    *sp = lean_sp;
   }
   return msg;
 }

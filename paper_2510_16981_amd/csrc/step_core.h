@@ -74,7 +74,8 @@ struct ScratchPlan {
 ScratchPlan scratch_plan(const Layout& lay, int full, const muonbp_options& o);
 
 // The allocation-free step's layout and scratch plan: layout_for's, or its
-// lean form where only that fits `limit` bytes.
+// lean form where only that fits `limit` bytes, or where that does not: which
+// steps fit (sp->total <= limit) is decided by the lean form alone.
 std::string scratch_layout(const std::vector<MatrixShape>& shapes, const muonbp_options& o, int full,
                            int64_t limit, bool momentum_aligned, Layout* lay, ScratchPlan* sp, bool* shape_error);
 
