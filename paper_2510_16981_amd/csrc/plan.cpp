@@ -425,10 +425,13 @@ double wave_k_launch_us(const std::vector<Problem>& probs, GemmKind kind) {
 // slice (0.5 alone on a CU); 32 x 32 tiles with the slices shared by the
 // waves, 5.7 a launch and 0.29 a slice.  Measured at 128 / 64 / 32: one 256 x
 // 256 unit 20 / 11 / 8, one 1024 x 1024 45 / 24 / 32, 144 tiles of 128 at K =
-// 4096 155 / 155 / 274, 1088 at K = 2048 443 / 464 / 988.  -1: a product over
-// more than kLongK terms, which takes the kernel that restarts its sums.
+// 4096 155 / 155 / 274, 1088 at K = 2048 443 / 464 / 988.  A shape whose tile
+// rows or columns do not fit 16 bits is out (build_layout's limit on the sides
+// leaves 64 x 64 tiles in).  -1: a product over more than kLongK terms, which
+// takes the kernel that restarts its sums.
 int32_t f32_split_variant(const std::vector<Problem>& probs, GemmKind kind) {
   int64_t tiles[3] = {0, 0, 0};
+  bool fits[3] = {true, true, true};
   static const int32_t variant[3] = {kGemmF32x128, kGemmF32x64, kGemmF32WaveK32};
   double slices = 0;
   for (const Problem& p : probs) {
@@ -439,13 +442,16 @@ int32_t f32_split_variant(const std::vector<Problem>& probs, GemmKind kind) {
       const int64_t tm = ceil_div(m, kGemmTileRows[variant[v]]), tn = ceil_div(c, kGemmTileCols[variant[v]]);
       const int64_t nt = kind == kApply ? tm * tn : tm * (tm + 1) / 2;
       tiles[v] += nt;
+      fits[v] = fits[v] && tm < kMaxTiles && tn < kMaxTiles;
       if (v == 0) slices += double(nt) * double(ceil_div(k, 32));
     }
   }
   slices /= double(tiles[0]);
   auto per_cu = [&](int v) { return std::max(1.0, double(tiles[v]) / kNumCUs); };
-  const double us[3] = {double(ceil_div(tiles[0], kNumCUs)) * (8 + 1.2 * slices),
-                        6.7 + std::max(0.5, 0.46 * per_cu(1)) * slices, 5.7 + 0.29 * per_cu(2) * slices};
+  double us[3] = {double(ceil_div(tiles[0], kNumCUs)) * (8 + 1.2 * slices),
+                  6.7 + std::max(0.5, 0.46 * per_cu(1)) * slices, 5.7 + 0.29 * per_cu(2) * slices};
+  for (int v = 0; v < 3; ++v)
+    if (!fits[v]) us[v] = std::numeric_limits<double>::infinity();
   return variant[std::min_element(us, us + 3) - us];
 }
 

@@ -10,7 +10,7 @@
 #include <map>
 #include <set>
 #include <string>
-#include <utility>
+#include <tuple>
 #include <vector>
 
 #include "plan.h"
@@ -33,7 +33,7 @@ int main(int argc, char** argv) {
       for (const Plan& plan : lay.plan)
         for (const GemmPhase& ph : plan.phases) {
           const int64_t bm = kGemmTileRows[ph.variant], bn = kGemmTileCols[ph.variant];
-          std::map<std::pair<int, int>, int> seen;
+          std::map<std::tuple<int, int64_t, int64_t>, int> seen;  // descriptor, row and column as the kernels decode them
           std::set<int> descs;
           int64_t load[kNumXCDs] = {}, total = 0, tiles = 0, longest = 0, unit = 0;
           for (size_t w = 0; w < ph.tiles.size(); ++w) {
@@ -42,7 +42,7 @@ int main(int argc, char** argv) {
               if (lean) return std::printf("empty entry in a lean plan\n"), 1;
               continue;
             }
-            ++seen[{t.prob, t.ij}];
+            ++seen[{t.prob, t.ij >> 16, t.ij & 0xffff}];
             descs.insert(t.prob);
             const Problem& p = plan.probs[size_t(t.prob / lay.desc_per_problem)];
             const int64_t cost = ((ph.kind == kGram ? p.L : p.S) + 31) / 32 + 14;
@@ -58,7 +58,7 @@ int main(int argc, char** argv) {
             int64_t n = 0;
             for (int64_t i = 0; i < tm; ++i)
               for (int64_t j = ph.kind == kApply ? 0 : i; j < tn; ++j, ++n)
-                if (seen[{dsc, int((i << 16) | j)}] != ph.nsplit) return std::printf("tile missing or twice\n"), 1;
+                if (seen[{dsc, i, j}] != ph.nsplit) return std::printf("tile missing or twice\n"), 1;
             want += n;
             unit = std::max(unit, longest * n);
           }

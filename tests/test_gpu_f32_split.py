@@ -77,3 +77,26 @@ def test_non_finite_input_spreads():
         u = [opt.get_update(k) for k in range(2)]
         assert not torch.isfinite(u[0]).any() and torch.isfinite(u[1]).all()
         opt.close()
+
+
+def test_columns_past_the_tile_index_of_narrow_tiles():
+    """2200000 columns are more 32-wide tiles than a tile index holds: beside
+    30000 small units (whose launches prefer those tiles) every column of U is
+    still written."""
+    import torch
+    from oracle import muonbp_oracle as O
+    from paper_2510_16981_amd import muonbp as mb
+    mats = [(1, 2200000, 1, 1), (8, 240000, 1, 30000)]
+    opt = mb.MuonBP(mats, 0, 0.02, 0.02, 0.95,
+                    options=mb.options_default(param_dtype=mb.F32, state_dtype=mb.F32, ns_dtype=mb.F32))
+    gen = torch.Generator().manual_seed(5)
+    g = [torch.randn(r, c, generator=gen) for r, c, _, _ in mats]
+    announce("1 x 2200000 beside 30000 units of 8 x 8, fp32 block step")
+    opt.step([torch.zeros(r, c, device="cuda") for r, c, _, _ in mats], [x.cuda() for x in g], 0)
+    u = [opt.get_update(k).double().cpu().numpy() for k in range(2)]
+    opt.close()
+    y = [x.double().numpy() for x in g]
+    ref = O.orthogonalize_via_ns(y[0])
+    assert rel(u[0], ref) <= TOL and rel(u[0][:, 2097152:], ref[:, 2097152:]) <= TOL
+    for c in (0, 8 * 12345, 240000 - 8):
+        assert rel(u[1][:, c:c + 8], O.orthogonalize_via_ns(y[1][:, c:c + 8])) <= TOL

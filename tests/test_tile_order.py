@@ -18,6 +18,9 @@ SHAPES = {
                   (14336, 4096, 8, 1, 1)],
     "three layers": [(2048, 2048, 1, 8, 3), (2048, 8192, 1, 8, 2), (8192, 2048, 1, 8, 5)],
     "long and short": [(64, 6656, 1, 1, 9), (1024, 4096, 1, 4, 3), (131, 64, 1, 1, 11), (2048, 2048, 1, 1, 7)],
+    # One row beside many small units (fp32 launches on 32 x 32 tiles): the
+    # row's tile columns at that width would not fit the 16 bits of a tile.
+    "widest": [(1, 2200000, 1, 1, 1), (8, 240000, 1, 30000, 1)],
 }
 
 
