@@ -113,6 +113,10 @@ struct TileRef {
   int32_t slot;  // K-split launches: index of the tile's partial sums and counter
   int32_t part;  // K-split launches: which share of the K slices
 };
+// Rows fill all of the upper 16 bits (the pack of a matrix of more than
+// 2097152 rows), so the word is not read as signed.
+constexpr int tile_row(int32_t ij) { return int(uint32_t(ij) >> 16); }
+constexpr int tile_col(int32_t ij) { return ij & 0xffff; }
 
 // Update source of one block for one plan: U window and RMS scale.
 struct UpdDesc {

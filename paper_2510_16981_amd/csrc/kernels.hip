@@ -364,7 +364,7 @@ __global__ __launch_bounds__(kThreads) void k_pack(
   __shared__ float s_fused;
   const TileRef t = tiles[blockIdx.x];
   const PackDesc d = pd[t.prob];
-  const int r0 = (t.ij >> 16) * 64, c0 = (t.ij & 0xffff) * 64;
+  const int r0 = tile_row(t.ij) * 64, c0 = tile_col(t.ij) * 64;
   if (fuse_scale) {  // uniform
     if (threadIdx.x < 64) {
       const float sc = unit_scale(partials, d.seg_begin, d.seg_end, eps);
@@ -803,7 +803,7 @@ __global__ __launch_bounds__(kThreads * KS) void k_ns_gemm(const GemmDesc* __res
   if (t.prob < 0) return;  // empty entry (balanced_order)
   const GemmDesc d = probs[t.prob];
   const float alpha = desc_alpha(d);
-  const int ti = t.ij >> 16, tj = t.ij & 0xffff;
+  const int ti = tile_row(t.ij), tj = tile_col(t.ij);
   const int m0 = ti * BM, n0 = tj * BN;
   const int grp = threadIdx.x >> 8;       // K group
   const int tid = threadIdx.x & 255;      // thread inside the group
@@ -1178,7 +1178,7 @@ __global__ __launch_bounds__(64 * WM * WN) void k_ns_gemm_dmap(const GemmDesc* _
   if (t.prob < 0) return;  // empty entry (balanced_order)
   const GemmDesc d = probs[t.prob];
   const float alpha = desc_alpha(d);
-  const int ti = t.ij >> 16, tj = t.ij & 0xffff;
+  const int ti = tile_row(t.ij), tj = tile_col(t.ij);
   const int m0 = ti * BM, n0 = tj * BN;
   const int tid = threadIdx.x, lane = tid & 63;
   const int wave = __builtin_amdgcn_readfirstlane(tid >> 6);
@@ -1606,7 +1606,7 @@ __global__ __launch_bounds__(kThreads) void k_ns_gemm_wavek(const GemmDesc* __re
   if (t.prob < 0) return;  // empty entry (balanced_order)
   const GemmDesc d = probs[t.prob];
   const float alpha = desc_alpha(d);
-  const int ti = t.ij >> 16, tj = t.ij & 0xffff;
+  const int ti = tile_row(t.ij), tj = tile_col(t.ij);
   const int m0 = ti * T, n0 = tj * T;
   const int lane = threadIdx.x & 63;
   const int wave = __builtin_amdgcn_readfirstlane(threadIdx.x >> 6);
@@ -1879,7 +1879,7 @@ __global__ __launch_bounds__(kThreads) void k_ns_gemm_f32(const GemmDesc* __rest
   if (t.prob < 0) return;  // empty entry (balanced_order)
   const GemmDesc d = probs[t.prob];
   const float alpha = desc_alpha(d);
-  const int ti = t.ij >> 16, tj = t.ij & 0xffff;
+  const int ti = tile_row(t.ij), tj = tile_col(t.ij);
   const int m0 = ti * BM, n0 = tj * BM;
   const int tid = threadIdx.x, lane = tid & 63, wave = tid >> 6;
   const int wm = wave >> 1, wn = wave & 1;
@@ -2043,7 +2043,7 @@ __global__ __launch_bounds__(kThreads) void k_ns_gemm_f32_wavek(const GemmDesc* 
   if (t.prob < 0) return;  // empty entry (balanced_order)
   const GemmDesc d = probs[t.prob];
   const float alpha = desc_alpha(d);
-  const int ti = t.ij >> 16, tj = t.ij & 0xffff;
+  const int ti = tile_row(t.ij), tj = tile_col(t.ij);
   const int m0 = ti * T, n0 = tj * T;
   const int lane = threadIdx.x & 63, r32 = lane & 31, hi = lane >> 5;
   const int wave = __builtin_amdgcn_readfirstlane(threadIdx.x >> 6);

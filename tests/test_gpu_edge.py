@@ -118,3 +118,22 @@ def test_largest_accepted_operand_against_oracle(dtype, ROWS, COLS, TOL):
     for cs, a, b in zip(cols, x0, x1):
         want = update_reference(a, u[:, cs], LR, WD, 1.0, dtype)
         assert ulp_distance(b, want, dtype) <= 1.0
+
+
+@pytest.mark.parametrize("dtype,bar", [("bf16", 2e-2), ("f32", 1e-4)])
+def test_more_than_32768_tile_rows_of_the_pack(dtype, bar):
+    """2200000 x 8 is packed (transposed) in 34375 rows of 64 x 64 tiles: the
+    last ones, whose index has the top bit of its 16 set, included."""
+    import torch
+    from paper_2510_16981_amd import muonbp as mb
+    dt = {"bf16": mb.BF16, "f32": mb.F32}[dtype]
+    gen = torch.Generator().manual_seed(7)
+    g = torch.randn(2200000, 8, generator=gen).to(torch.bfloat16 if dtype == "bf16" else torch.float32)
+    announce(f"2200000 x 8 {dtype}")
+    opt = mb.MuonBP([(2200000, 8, 1, 1)], 1, LR, LR, MU, WD,
+                    options=mb.options_default(param_dtype=dt, state_dtype=dt, ns_dtype=dt))
+    opt.step([torch.zeros_like(g).cuda()], [g.cuda()], 0)
+    u = opt.get_update(0).double().cpu().numpy()
+    opt.close()
+    ref = O.orthogonalize_via_ns(g.double().numpy())
+    assert rel(u, ref) <= bar and rel(u[32768 * 64:], ref[32768 * 64:]) <= bar

@@ -21,6 +21,8 @@ SHAPES = {
     # One row beside many small units (fp32 launches on 32 x 32 tiles): the
     # row's tile columns at that width would not fit the 16 bits of a tile.
     "widest": [(1, 2200000, 1, 1, 1), (8, 240000, 1, 30000, 1)],
+    # More than 32768 tile rows of the pack.
+    "tallest": [(2200000, 8, 1, 1, 1)],
 }
 
 
