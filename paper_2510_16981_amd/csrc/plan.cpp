@@ -419,6 +419,36 @@ double wave_k_launch_us(const std::vector<Problem>& probs, GemmKind kind) {
   return 2.4 + double(full) * two + (rest == 0 ? 0.0 : rest <= kNumCUs ? one : two);
 }
 
+// Whether kGemmWaveK64 may take a launch whose best DMA kernel is `dma`: where
+// neither that kernel nor its K split over three workgroups is the faster one
+// (measured per launch, us; slices are the longest product's).
+//  * Up to three tiles per CU: 720 tiles of 10 / 80 slices 15.4 / 36.6 against
+//    17.9 / 42.9; beyond, 1440 of 10 24.5 against 20.5, 960 of 106 60.8 against
+//    50.8.
+//  * With more than one tile per CU up to 128 slices: 440 of 112 and 440 of 80
+//    0.92 of the DMA kernel's time, 275 of 160 49.8 against 43.7, 360 of 240
+//    70.2 against 60.6 (0.81 to 1.16 from 144 slices on, 1.02 in the mean).
+//  * Where the split kernel would run at one workgroup per CU (three per tile):
+//    with more than one tile per CU not at all (312 of 128 / 512 slices 31.3 /
+//    129.6 against 25.2 / 63.4 split), else below 320 slices (144 of 192 / 256
+//    25.8 / 29.7 against 26.6 / 32.6; 84 of 384 52.6 against 44.7), or below
+//    192 with fewer than 20 tiles (12 of 128 18.9 against 19.6; 12 of 192 / 384
+//    / 3125 28.3 / 53.1 / 427.6 against 23.6 / 35.5 / 265.5).
+bool wave_k_allowed(const std::vector<Problem>& probs, GemmKind kind, int32_t dma) {
+  const int64_t tiles = count_tiles(probs, kind, kGemmWaveK64);
+  int64_t slices = 0;
+  for (const Problem& p : probs) {
+    int64_t m, c, k;
+    gemm_dims(p, kind, &m, &c, &k);
+    slices = std::max(slices, ceil_div(k, 32));
+  }
+  const int32_t split = choose_split(probs, kind, dma, 0);
+  const bool split_fits = split > 1 && split * count_tiles(probs, kind, dma) <= kNumCUs;
+  if (tiles > 3 * kNumCUs) return false;
+  if (tiles > kNumCUs) return slices <= 128 && !split_fits;
+  return !split_fits || slices < (tiles < 20 ? 192 : 320);
+}
+
 // The kernel of one fp32 launch, by time models of the three tile shapes whose
 // operands are split into bf16 parts, in us: 128 x 128 tiles, one per CU at a
 // time, 8 + 1.2 a 32-column slice each; 64 x 64 tiles, 6.7 a launch and 0.46 a
@@ -510,7 +540,8 @@ int32_t choose_variant(const std::vector<Problem>& probs, GemmKind kind, int til
     }
     // The 128 x 128 model above is for full launches: where few CUs are busy
     // a launch takes 1.5-3 us less, hence the margin.
-    if (wave_k && wave_k_launch_us(probs, kind) < 0.9 * best_us) return kGemmWaveK64;
+    if (wave_k && wave_k_launch_us(probs, kind) < 0.9 * best_us && wave_k_allowed(probs, kind, best))
+      return kGemmWaveK64;
     if (best == kGemmDmaP192x256) best = kGemmDmaP192x256W8;
     if (best == kGemmDmaP256x192) best = kGemmDmaP256x192W8;
     return best;
