@@ -133,7 +133,10 @@ typedef struct {
                                checking the momentum + workspace + split sums
                                before any HIP call; 0 = no limit (default).
                                muonbp_plan_info.device_bytes is the size of
-                               those three. */
+                               those three for the plan chosen without a
+                               limit; where that does not fit, a plan with
+                               smaller tables (and, for some shapes, a smaller
+                               workspace) is tried. */
   int32_t gram_iteration;   /* how the K NS iterations of a unit run (the
                                result is Alg. 2's, up to rounding).  Each
                                iteration multiplies Z by a polynomial of its

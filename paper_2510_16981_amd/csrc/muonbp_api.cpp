@@ -347,24 +347,9 @@ static muonbp_status create_ctx(const muonbp_matrix* mats, int32_t n_mats, int64
     free_ctx(c);
     return MUONBP_E_NOMEM;
   }
-  if (o.device_memory_limit > 0) {
-    // Both forms of the plan have to fit: the lean one decides, as before the
-    // other existed, and the other falls back to it.
-    bool over = context_bulk_bytes(c->lay, o) > o.device_memory_limit;
-    if (!over && !lean) {
-      try {
-        Layout other;
-        bool shape_err = false;
-        over = !layout_for(shapes, o, &other, &shape_err, true, true).empty() ||
-               context_bulk_bytes(other, o) > o.device_memory_limit;
-      } catch (const std::bad_alloc&) {
-        over = true;
-      }
-    }
-    if (over) {
-      free_ctx(c);
-      return MUONBP_E_NOMEM;
-    }
+  if (o.device_memory_limit > 0 && context_bulk_bytes(c->lay, o) > o.device_memory_limit) {
+    free_ctx(c);
+    return MUONBP_E_NOMEM;
   }
   c->opt = o;
   c->period = period;

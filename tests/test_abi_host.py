@@ -10,6 +10,7 @@ import re
 
 import numpy as np
 import pytest
+import torch
 
 from oracle import muonbp_oracle as O
 from paper_2510_16981_amd import muonbp as mb
@@ -87,6 +88,20 @@ def test_device_memory_limit_refuses_before_gpu(lib):
         st, ctx = _create(lib, mats, opt=mb.options_default(device_memory_limit=limit))
         assert st == 4 and not ctx.value
     assert _create(lib, mats, opt=mb.options_default(device_memory_limit=-1))[0] == 1
+
+
+@pytest.mark.parametrize("mats", [[(4095, 14335, 1, 1)], [(999, 3001, 1, 1)], [(3001, 999, 1, 1)],
+                                  [(1001, 4003, 1, 1), (650, 975, 1, 3)], [(2048, 6144, 1, 8), (129, 1000, 1, 1)]])
+def test_device_memory_limit_accepts_the_described_plan(lib, mats):
+    """device_bytes and room for the tables are enough, also where the plan
+    with the smallest tables would need more than that (it keeps Z^T pairs of
+    units with odd sides).  Past the limit's check, creation fails on the first
+    HIP call here."""
+    if torch.cuda.is_available():
+        pytest.skip("tells a refusal from the lack of a GPU")
+    info = mb.describe_plan(mats, True)
+    for limit, want in ((info.device_bytes + (64 << 20), 5), (info.device_bytes, 5), (1, 4)):
+        assert _create(lib, mats, opt=mb.options_default(device_memory_limit=limit))[0] == want
 
 
 def test_create_rejects_bad_arguments_before_gpu(lib):
