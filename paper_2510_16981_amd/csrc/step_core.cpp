@@ -311,15 +311,12 @@ std::string scratch_layout(const std::vector<MatrixShape>& shapes, const muonbp_
   std::string msg = layout_for(shapes, o, lay, shape_error, momentum_aligned, false);
   if (!msg.empty()) return msg;
   *sp = scratch_plan(*lay, full, o);
-  // The lean form is less than three times as large (Z and Z^T twice instead of
-  // Z twice, and the sums of a K split), so it need not be asked below a third
-  // of the limit.
-  if (3 * sp->total <= limit) return msg;
+  if (sp->total <= limit) return msg;
   Layout lean;
   msg = layout_for(shapes, o, &lean, shape_error, momentum_aligned, true);
   if (!msg.empty()) return msg;
   const ScratchPlan lean_sp = scratch_plan(lean, full, o);
-  if (lean_sp.total > limit || sp->total > limit) {
+  if (lean_sp.total < sp->total) {
     *lay = std::move(lean);
     *sp = lean_sp;
   }

@@ -73,9 +73,9 @@ struct ScratchPlan {
 };
 ScratchPlan scratch_plan(const Layout& lay, int full, const muonbp_options& o);
 
-// The allocation-free step's layout and scratch plan: layout_for's, or its
-// lean form where only that fits `limit` bytes, or where that does not: which
-// steps fit (sp->total <= limit) is decided by the lean form alone.
+// The allocation-free step's layout and scratch plan: layout_for's, or its lean
+// form where the first does not fit `limit` bytes and the lean one is smaller.
+// The step fits where sp->total <= limit.
 std::string scratch_layout(const std::vector<MatrixShape>& shapes, const muonbp_options& o, int full,
                            int64_t limit, bool momentum_aligned, Layout* lay, ScratchPlan* sp, bool* shape_error);
 

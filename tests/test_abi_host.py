@@ -471,6 +471,20 @@ def test_static_step_refuses_on_the_host(lib):
     assert lib.muonbp_step_static(mats, 1, bad, fake, ctypes.c_void_p(256), *args) == 1
 
 
+@pytest.mark.parametrize("mat", [(1801, 9001, 1, 1), (9001, 1801, 1, 1), (1999, 8001, 1, 1)])
+def test_static_step_takes_the_described_plan(lib, mat):
+    """A step is refused only where its own plan does not fit the scratch array:
+    with odd sides the plan with the smallest tables is the larger one (Z^T pairs)
+    and would not.  The call then fails on the first HIP call here."""
+    info = mb.describe_plan([mat], True)
+    assert info.workspace_bytes < info.static_scratch_bytes <= mb.STATIC_SCRATCH_BYTES
+    if torch.cuda.is_available():
+        pytest.skip("tells a refusal from the lack of a GPU")
+    fake = (ctypes.c_void_p * 1)(256)
+    assert lib.muonbp_step_static(mb._mats([mat]), 1, fake, fake, ctypes.c_void_p(256), 0, 1, 0.01, 0.02, 0.9,
+                                  0.0, None, None) == 5
+
+
 def test_static_scratch_fits_the_qkv_workload(lib):
     """The static scratch array is sized for one 2048 x 6144 matrix in
     2048 x 768 shards, in both plans."""
