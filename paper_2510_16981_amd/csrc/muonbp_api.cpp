@@ -282,7 +282,9 @@ muonbp_status muonbp_describe_plan(const muonbp_matrix* mats, int32_t n_mats,
   ScratchPlan sp;
   bool shape_err = false;
   try {
-    if (!layout_for(shapes, o, &lay, &shape_err).empty() ||
+    if (!layout_for(shapes, o, &lay, &shape_err).empty()) return shape_err ? MUONBP_E_SHAPE : MUONBP_E_INVALID;
+    sp = scratch_plan(lay, full, o);
+    if (sp.total > MUONBP_STATIC_SCRATCH_BYTES &&
         !scratch_layout(shapes, o, full, MUONBP_STATIC_SCRATCH_BYTES, true, &static_lay, &sp, &shape_err).empty())
       return shape_err ? MUONBP_E_SHAPE : MUONBP_E_INVALID;
   } catch (const std::bad_alloc&) {

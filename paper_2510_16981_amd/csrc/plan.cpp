@@ -4,7 +4,6 @@
 #include "plan.h"
 
 #include <algorithm>
-#include <iterator>
 #include <limits>
 #include <utility>
 
@@ -214,24 +213,21 @@ std::vector<TileRef> balanced_order(const std::vector<TileRef>& logical, std::ve
       load[x] += n * per;
       u.begin += n;
     }
-  int64_t most = 0;
-  std::vector<TileRef> run[kNumXCDs];
+  int64_t size = 0;
   for (int x = 0; x < kNumXCDs; ++x) {
     if (reverse) std::reverse(share[x].begin(), share[x].end());
     std::stable_sort(share[x].begin(), share[x].end(), longer);
-    for (const UnitTiles& u : share[x]) {
-      const auto b = logical.begin() + u.begin, e = logical.begin() + u.end;
-      if (reverse)
-        run[x].insert(run[x].end(), std::make_reverse_iterator(e), std::make_reverse_iterator(b));
-      else
-        run[x].insert(run[x].end(), b, e);
-    }
-    most = std::max(most, int64_t(run[x].size()));
+    int64_t n = 0;
+    for (const UnitTiles& u : share[x]) n += u.end - u.begin;
+    if (n > 0) size = std::max(size, (n - 1) * kNumXCDs + x + 1);
   }
-  std::vector<TileRef> out(size_t(most * kNumXCDs), TileRef{-1, 0, 0, 0});
-  for (int x = 0; x < kNumXCDs; ++x)
-    for (size_t j = 0; j < run[x].size(); ++j) out[j * kNumXCDs + x] = run[x][j];
-  while (!out.empty() && out.back().prob < 0) out.pop_back();
+  std::vector<TileRef> out(size_t(size), TileRef{-1, 0, 0, 0});
+  for (int x = 0; x < kNumXCDs; ++x) {
+    size_t w = size_t(x);
+    for (const UnitTiles& u : share[x])
+      for (int64_t j = 0; j < u.end - u.begin; ++j, w += kNumXCDs)
+        out[w] = logical[size_t(reverse ? u.end - 1 - j : u.begin + j)];
+  }
   return out;
 }
 
@@ -256,48 +252,76 @@ void build_phases(Plan* plan, int ns_steps, int poly_slots, int desc_per_problem
   plan->split_floats = plan->split_slots = 0;
   const int32_t np = int32_t(plan->probs.size());
   using Item = std::pair<int32_t, int32_t>;  // (problem, descriptor slot)
+  // The workgroup orders of this plan, with an item's number in place of its
+  // descriptor: launches of one kind over the same problems differ in the
+  // descriptors only.
+  struct Order {
+    GemmKind kind;
+    bool reverse;
+    std::vector<int32_t> probs;
+    bool long_k;
+    std::vector<TileRef> tiles;
+  };
+  std::vector<Order> orders;
+  auto order_for = [&](GemmKind kind, bool reverse, const std::vector<Item>& items) -> const Order& {
+    for (const Order& o : orders)
+      if (o.kind == kind && o.reverse == reverse &&
+          std::equal(items.begin(), items.end(), o.probs.begin(), o.probs.end(),
+                     [](const Item& it, int32_t pi) { return it.first == pi; }))
+        return o;
+    const int32_t variant = plan->variant[kind], nsplit = plan->nsplit[kind];
+    Order o{kind, reverse, {}, false, {}};
+    std::vector<UnitTiles> units;
+    std::vector<TileRef> logical;
+    // Items of a launch are the plan's problems, or each of them twice.
+    logical.reserve(size_t(plan->tiles_per_iter[kind]));
+    for (const Item& it : items) {
+      const Problem& p = plan->probs[size_t(it.first)];
+      int64_t m, n, k;
+      gemm_dims(p, kind, &m, &n, &k);
+      if (ns_elem_bytes == 4 && !gemm_is_dmap(variant)) o.long_k = o.long_k || k > kLongK;
+      const int64_t t0 = int64_t(logical.size());
+      append_tiles(p, kind, variant, int32_t(o.probs.size()), &logical);
+      units.push_back(UnitTiles{t0, int64_t(logical.size()), ceil_div(k, 32)});
+      o.probs.push_back(it.first);
+    }
+    if (nsplit > 1) {
+      // The shares of one tile are adjacent, so that the XCD order below
+      // keeps them on one XCD (one L2) as a rule.
+      std::vector<TileRef> parts;
+      parts.reserve(logical.size() * size_t(nsplit));
+      for (size_t ti = 0; ti < logical.size(); ++ti)
+        for (int32_t q = 0; q < nsplit; ++q)
+          parts.push_back(TileRef{logical[ti].prob, logical[ti].ij, int32_t(ti), q});
+      plan->split_slots = std::max<int64_t>(plan->split_slots, int64_t(logical.size()));
+      plan->split_floats = std::max<int64_t>(
+          plan->split_floats, int64_t(logical.size()) * nsplit * kGemmTileRows[variant] * kGemmTileCols[variant]);
+      logical.swap(parts);
+    }
+    // A launch of several rounds: the XCDs' shares balanced, and the units
+    // walked the other way round in every second launch.
+    if (!lean && nsplit == 1 && int64_t(logical.size()) > kNumCUs)
+      o.tiles = balanced_order(logical, std::move(units), reverse);
+    else
+      o.tiles = xcd_order(logical);
+    orders.push_back(std::move(o));
+    return orders.back();
+  };
   auto add_phase = [&](GemmKind kind, const std::vector<Item>& items) {
     if (items.empty()) return;
-    std::vector<UnitTiles> units;
+    const Order& o = order_for(kind, plan->phases.size() % 2 == 1, items);
     GemmPhase phase;
     phase.variant = plan->variant[kind];
     phase.kind = kind;
     phase.nsplit = plan->nsplit[kind];
     phase.nn = kind == kApply && plan->nn_apply;
-    std::vector<TileRef> logical;
-    for (const Item& it : items) {
-      const Problem& p = plan->probs[size_t(it.first)];
-      if (ns_elem_bytes == 4 && !gemm_is_dmap(phase.variant)) {
-        int64_t m, n, k;
-        gemm_dims(p, kind, &m, &n, &k);
-        phase.long_k = phase.long_k || k > kLongK;
+    phase.long_k = o.long_k;
+    phase.tiles = o.tiles;
+    for (TileRef& t : phase.tiles)
+      if (t.prob >= 0) {
+        const Item& it = items[size_t(t.prob)];
+        t.prob = it.first * desc_per_problem + it.second;
       }
-      const int64_t t0 = int64_t(logical.size());
-      append_tiles(p, kind, phase.variant, it.first * desc_per_problem + it.second, &logical);
-      int64_t m, n, k;
-      gemm_dims(p, kind, &m, &n, &k);
-      units.push_back(UnitTiles{t0, int64_t(logical.size()), ceil_div(k, 32)});
-    }
-    if (phase.nsplit > 1) {
-      // The shares of one tile are adjacent, so that the XCD order below
-      // keeps them on one XCD (one L2) as a rule.
-      std::vector<TileRef> parts;
-      parts.reserve(logical.size() * size_t(phase.nsplit));
-      for (size_t ti = 0; ti < logical.size(); ++ti)
-        for (int32_t q = 0; q < phase.nsplit; ++q)
-          parts.push_back(TileRef{logical[ti].prob, logical[ti].ij, int32_t(ti), q});
-      plan->split_slots = std::max<int64_t>(plan->split_slots, int64_t(logical.size()));
-      plan->split_floats = std::max<int64_t>(
-          plan->split_floats, int64_t(logical.size()) * phase.nsplit *
-                                  kGemmTileRows[phase.variant] * kGemmTileCols[phase.variant]);
-      logical.swap(parts);
-    }
-    // A launch of several rounds: the XCDs' shares balanced, and the units
-    // walked the other way round in every second launch.
-    if (!lean && phase.nsplit == 1 && int64_t(logical.size()) > kNumCUs)
-      phase.tiles = balanced_order(logical, std::move(units), plan->phases.size() % 2 == 1);
-    else
-      phase.tiles = xcd_order(logical);
     plan->phases.push_back(std::move(phase));
   };
   for (int iter = 0; iter < ns_steps; ++iter) {
@@ -606,7 +630,7 @@ double ns_unit_dense_flops(int64_t S, int64_t L, int K) {
 std::string build_layout(const MatrixShape* mats, int32_t n_mats,
                          int ns_elem_bytes, int ns_steps, int poly_slots, int tile_policy,
                          int k_split, int apply_mode, Layout* out, bool* shape_error, int gram_mode,
-                         bool in_place_input, bool lean, bool quintic) {
+                         bool in_place_input, bool lean, bool quintic, int lists) {
   *shape_error = false;
   if (!mats || n_mats <= 0) return "mats must be a non-empty array";
   if (ns_steps < 0) return "ns_steps must be >= 0";
@@ -760,7 +784,8 @@ std::string build_layout(const MatrixShape* mats, int32_t n_mats,
       p.gram = gram_mode != 1 && ns_elem_bytes == 2 && plan.nn_apply && ns_steps >= 2 &&
                (quintic || chunks) && (gram_mode == 2 || (p.S >= kGramMinS && 4 * p.L >= 5 * p.S));
     if (gram_mode == 0 && padded && quintic) unify_iteration(&plan.probs, ns_steps);
-    int64_t cursor = 0;
+    int64_t cursor = 0, packed = 0;
+    const bool with_lists = lists < 0 || lists == full;
     for (int32_t pi = 0; pi < int32_t(plan.probs.size()); ++pi) {
       Problem& p = plan.probs[pi];
       // The momentum window as a GEMM operand: rows of whole 16-byte chunks
@@ -771,14 +796,16 @@ std::string build_layout(const MatrixShape* mats, int32_t n_mats,
                    mm.cols % 8 == 0 && (!padded || p.cols % 8 == 0) && mom_off % 8 == 0 &&
                    p.rows * mm.cols * ns_elem_bytes < kMaxOperandBytes;
       if (!place_problem(&p, &cursor, align_elems, plan.nn_apply)) return "workspace too large";
-      if (!p.in_place) add_pack_tiles(&plan, pi);
+      if (!p.in_place) {
+        packed += ceil_div(p.rows, kPackTile) * ceil_div(p.cols, kPackTile);
+        if (with_lists) add_pack_tiles(&plan, pi);
+      }
       plan.ns_flops += ns_unit_flops(p.S, p.L, ns_steps, p.gram);
       plan.ns_dense_flops += ns_unit_dense_flops(p.S, p.L, ns_steps);
     }
     plan.ws_elems = cursor;
-    build_phases(&plan, ns_steps, poly_slots, L.desc_per_problem, ns_elem_bytes, lean);
-    if (plan.pack_tiles.size() > size_t(std::numeric_limits<int32_t>::max() / 2))
-      return "too many tiles";
+    if (with_lists) build_phases(&plan, ns_steps, poly_slots, L.desc_per_problem, ns_elem_bytes, lean);
+    if (packed > int64_t(std::numeric_limits<int32_t>::max() / 2)) return "too many tiles";
   }
   *out = std::move(L);
   return "";

@@ -178,11 +178,13 @@ struct Layout {
 // Gram-space iteration's S x S buffers are more than the Z^T pair it keeps
 // below L = 1.5 S).
 // quintic: every iteration's coefficients are the paper's (2, -1.5, 0.5).
+// lists: the plan (0, 1) whose launches and pack tiles are wanted, -1 = both.
+// Both are checked and placed all the same.
 std::string build_layout(const MatrixShape* mats, int32_t n_mats,
                          int ns_elem_bytes, int ns_steps, int poly_slots, int tile_policy,
                          int k_split, int apply_mode,
                          Layout* out, bool* shape_error, int gram_mode = 0,
-                         bool in_place_input = false, bool lean = false, bool quintic = true);
+                         bool in_place_input = false, bool lean = false, bool quintic = true, int lists = -1);
 
 // Descriptor slot of segment sg's apply on a Gram-space unit (Z[1 - z] =
 // Q[q] Z[z] with z = sg mod 2, q the buffer of the segment's last Q, and

@@ -70,7 +70,7 @@ std::string check_mats(const muonbp_matrix* mats, int32_t n_mats, std::vector<Ma
 }
 
 std::string layout_for(const std::vector<MatrixShape>& shapes, const muonbp_options& o, Layout* out,
-                       bool* shape_error, bool momentum_aligned, bool lean) {
+                       bool* shape_error, bool momentum_aligned, bool lean, int lists) {
   // The NS input is the momentum itself when it is stored as the NS dtype
   // and no Nesterov blend is formed.
   const bool in_place = momentum_aligned && o.state_dtype == MUONBP_BF16 && o.ns_dtype == MUONBP_BF16 &&
@@ -83,7 +83,7 @@ std::string layout_for(const std::vector<MatrixShape>& shapes, const muonbp_opti
   }
   return build_layout(shapes.data(), int32_t(shapes.size()), int(dtype_size(o.ns_dtype)), o.ns_steps,
                       poly_slots(o), o.tile_policy, o.k_split, o.apply_mode, out, shape_error,
-                      o.gram_iteration, in_place, lean, quintic);
+                      o.gram_iteration, in_place, lean, quintic, lists);
 }
 
 void build_plan_host_tables(const Layout& lay, const muonbp_options& o, int full, void* ws_base,
@@ -308,12 +308,12 @@ ScratchPlan scratch_plan(const Layout& lay, int full, const muonbp_options& o) {
 
 std::string scratch_layout(const std::vector<MatrixShape>& shapes, const muonbp_options& o, int full,
                            int64_t limit, bool momentum_aligned, Layout* lay, ScratchPlan* sp, bool* shape_error) {
-  std::string msg = layout_for(shapes, o, lay, shape_error, momentum_aligned, false);
+  std::string msg = layout_for(shapes, o, lay, shape_error, momentum_aligned, false, full);
   if (!msg.empty()) return msg;
   *sp = scratch_plan(*lay, full, o);
   if (sp->total <= limit) return msg;
   Layout lean;
-  msg = layout_for(shapes, o, &lean, shape_error, momentum_aligned, true);
+  msg = layout_for(shapes, o, &lean, shape_error, momentum_aligned, true, full);
   if (!msg.empty()) return msg;
   const ScratchPlan lean_sp = scratch_plan(lean, full, o);
   if (lean_sp.total < sp->total) {

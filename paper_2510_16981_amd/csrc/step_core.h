@@ -35,10 +35,10 @@ std::string check_mats(const muonbp_matrix* mats, int32_t n_mats, std::vector<Ma
 
 // build_layout with the NS settings of the options.  momentum_aligned: the
 // momentum arena starts on a 16-byte boundary (always for a context's own
-// arena), a condition for reading it in place as the NS input.  lean: as
-// build_layout has it.
+// arena), a condition for reading it in place as the NS input.  lean,
+// lists: as build_layout has them.
 std::string layout_for(const std::vector<MatrixShape>& shapes, const muonbp_options& o, Layout* out,
-                       bool* shape_error, bool momentum_aligned = true, bool lean = false);
+                       bool* shape_error, bool momentum_aligned = true, bool lean = false, int lists = -1);
 
 // Host form of one plan's device tables, the NS workspace starting at `ws`,
 // the momentum arena at `mom` and the per-problem scales at `scales` (both

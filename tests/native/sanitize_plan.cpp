@@ -49,6 +49,16 @@ bool one(const std::vector<MatrixShape>& mats, const muonbp_options& o, bool exp
     checksum += int64_t(h.descs.size()) + int64_t(h.upd.size()) + sp.total;
     for (const GemmPhase& ph : lay.plan[full].phases)
       for (const TileRef& t : ph.tiles) checksum += t.prob ^ t.ij;
+    // The allocation-free step plans on every call: the same plan, and no
+    // launches of the other one.
+    Layout one_lay;
+    ScratchPlan one_sp;
+    if (!scratch_layout(mats, o, full, int64_t(1) << 50, true, &one_lay, &one_sp, &shape_err).empty() ||
+        one_sp.total != sp.total || one_lay.plan[full].phases.size() != lay.plan[full].phases.size() ||
+        !one_lay.plan[1 - full].phases.empty() || !one_lay.plan[1 - full].pack_tiles.empty()) {
+      std::printf("scratch_layout: not the one plan\n");
+      return false;
+    }
   }
   checksum += int64_t(block_descs(lay).size()) + (layout_vectorizable(lay) ? 1 : 0);
   return true;
