@@ -75,6 +75,7 @@ struct muonbp_ctx {
   PlanDev pd[2];
   std::vector<void*> allocs;
   int64_t allocated = 0;  // bytes in allocs (device_memory_limit)
+  bool over_limit = false;  // an allocation was refused by it, without a HIP call
 
   PtrRing ptrs;  // caller's param / grad pointers of the current step
 
@@ -129,7 +130,10 @@ hipError_t dev_alloc(muonbp_ctx* c, void** p, size_t bytes) {
   *p = nullptr;
   if (bytes == 0) bytes = 256;
   const int64_t limit = c->opt.device_memory_limit;
-  if (limit > 0 && int64_t(bytes) > limit - c->allocated) return hipErrorOutOfMemory;
+  if (limit > 0 && int64_t(bytes) > limit - c->allocated) {
+    c->over_limit = true;
+    return hipErrorOutOfMemory;
+  }
   hipError_t e = hipMalloc(p, bytes);
   if (e == hipSuccess) {
     c->allocs.push_back(*p);
@@ -318,10 +322,11 @@ muonbp_status muonbp_describe_plan(const muonbp_matrix* mats, int32_t n_mats,
   return MUONBP_OK;
 }
 
-// lean: with the plans of layout_for's lean form.
+// lean: with the plans of layout_for's lean form.  hip_oom: set where a HIP
+// allocation ran out of memory (not the limit).
 static muonbp_status create_ctx(const muonbp_matrix* mats, int32_t n_mats, int64_t period, float lr_block,
                                 float lr_full, float momentum, float weight_decay, const muonbp_options* opt,
-                                void* hip_stream, bool lean, muonbp_ctx** out) {
+                                void* hip_stream, bool lean, bool* hip_oom, muonbp_ctx** out) {
   *out = nullptr;
   muonbp_options o;
   muonbp_options_default(&o);
@@ -373,6 +378,7 @@ static muonbp_status create_ctx(const muonbp_matrix* mats, int32_t n_mats, int64
   }
   auto bail = [&](hipError_t err, const char* what) {
     const muonbp_status st = (err == hipErrorOutOfMemory) ? MUONBP_E_NOMEM : MUONBP_E_HIP;
+    *hip_oom = err == hipErrorOutOfMemory && !c->over_limit;
     free_ctx(c);
     (void)what;
     return st;
@@ -421,14 +427,16 @@ muonbp_status muonbp_create(const muonbp_matrix* mats, int32_t n_mats, int64_t p
                             float lr_block, float lr_full, float momentum, float weight_decay,
                             const muonbp_options* opt, void* hip_stream, muonbp_ctx** out) {
   if (!out) return MUONBP_E_INVALID;
-  muonbp_status st = MUONBP_E_NOMEM;
+  bool hip_oom = false;
+  muonbp_status st = create_ctx(mats, n_mats, period, lr_block, lr_full, momentum, weight_decay, opt, hip_stream,
+                                false, &hip_oom, out);
+  if (st != MUONBP_E_NOMEM) return st;
   // Out of memory (device_memory_limit, or the device's own): once more with
-  // the smaller plans.
-  for (int lean = 0; lean < 2 && st == MUONBP_E_NOMEM; ++lean) {
-    st = create_ctx(mats, n_mats, period, lr_block, lr_full, momentum, weight_decay, opt, hip_stream, lean != 0, out);
-    if (st == MUONBP_E_NOMEM && lean == 0) (void)hipGetLastError();  // the failed allocation's
-  }
-  return st;
+  // the smaller plans.  A failed HIP allocation's error is dropped, any other
+  // pending one is the caller's.
+  if (hip_oom) (void)hipGetLastError();
+  return create_ctx(mats, n_mats, period, lr_block, lr_full, momentum, weight_decay, opt, hip_stream, true, &hip_oom,
+                    out);
 }
 
 muonbp_status muonbp_step(muonbp_ctx* c, void* const* params, const void* const* grads, int64_t step) {

@@ -139,3 +139,19 @@ def test_device_memory_limit_out_of_memory_frees_everything():
     st, ctx = create(bulk + (64 << 20))
     assert st == 0 and ctx.value
     lib.muonbp_destroy(ctx)
+
+
+def test_refusal_by_the_memory_limit_keeps_the_callers_hip_error():
+    """The check of the budget comes before any HIP call: an error of the
+    caller's that it has not polled yet is still there afterwards."""
+    from paper_2510_16981_amd import muonbp as mb
+    lib = mb.load_library()
+    assert lib.hipGetLastError() in (0, 1) and lib.hipPeekAtLastError() == 0
+    pending = lib.hipSetDevice(9999)
+    assert pending != 0 and lib.hipPeekAtLastError() == pending
+    ctx = ctypes.c_void_p()
+    o = mb.options_default(device_memory_limit=1)
+    announce("muonbp_create over its budget with a pending HIP error")
+    assert lib.muonbp_create(mb._mats(MATS), len(MATS), 1, 0.01, 0.02, 0.95, 0.1, ctypes.byref(o), None,
+                             ctypes.byref(ctx)) == 4
+    assert lib.hipGetLastError() == pending
