@@ -1,10 +1,11 @@
 // Host-only sweep of the planner under AddressSanitizer and UBSan (built by
 // tests/test_sanitize_host.py with g++; no GPU, no HIP call): build_layout
-// over the benchmark workloads' shapes, every tile policy, K split and apply
-// mode, both NS dtypes, ragged and degenerate shapes and the bad-argument
-// cases, then the host form of both plans' device tables and the scratch
-// layout of the allocation-free step.  Prints one line per case family and
-// "ok" at the end; any sanitizer report aborts with a non-zero status.
+// over the benchmark workloads' shapes, in the preferred and the lean form,
+// every tile policy, K split and apply mode, both NS dtypes, ragged and
+// degenerate shapes and the bad-argument cases, then the host form of both
+// plans' device tables and the scratch layout of the allocation-free step.
+// Prints one line per case family and "ok" at the end; any sanitizer report
+// aborts with a non-zero status.
 #include <cstdio>
 #include <cstring>
 #include <string>
@@ -31,11 +32,12 @@ muonbp_options defaults() {
 
 int64_t checksum = 0;
 
-// One plan set: layout, both plans' host tables, both scratch layouts.
-bool one(const std::vector<MatrixShape>& mats, const muonbp_options& o, bool expect_ok) {
+// One plan set: layout (the preferred form or the lean one), both plans' host
+// tables, both scratch layouts.
+bool one_form(const std::vector<MatrixShape>& mats, const muonbp_options& o, bool expect_ok, bool lean) {
   Layout lay;
   bool shape_err = false;
-  const std::string msg = layout_for(mats, o, &lay, &shape_err);
+  const std::string msg = layout_for(mats, o, &lay, &shape_err, true, lean);
   if (msg.empty() != expect_ok) {
     std::printf("unexpected result (%s): %s\n", expect_ok ? "want ok" : "want error", msg.c_str());
     return false;
@@ -49,6 +51,7 @@ bool one(const std::vector<MatrixShape>& mats, const muonbp_options& o, bool exp
     checksum += int64_t(h.descs.size()) + int64_t(h.upd.size()) + sp.total;
     for (const GemmPhase& ph : lay.plan[full].phases)
       for (const TileRef& t : ph.tiles) checksum += t.prob ^ t.ij;
+    if (lean) continue;
     // The allocation-free step plans on every call: the same plan, and no
     // launches of the other one.
     Layout one_lay;
@@ -62,6 +65,10 @@ bool one(const std::vector<MatrixShape>& mats, const muonbp_options& o, bool exp
   }
   checksum += int64_t(block_descs(lay).size()) + (layout_vectorizable(lay) ? 1 : 0);
   return true;
+}
+
+bool one(const std::vector<MatrixShape>& mats, const muonbp_options& o, bool expect_ok) {
+  return one_form(mats, o, expect_ok, false) && one_form(mats, o, expect_ok, true);
 }
 
 }  // namespace
