@@ -150,12 +150,20 @@ typedef struct {
                                iterations then run in segments of at most 3,
                                each from a fresh Gram of the current Z.
                                0 = that Gram-space iteration on the units
-                               where it saves time (bf16 NS, the row-major
-                               apply, K >= 2, S >= 128 and L >= 1.25 S), as
-                               printed elsewhere (default); 1 = as printed
-                               everywhere; 2 = the Gram-space iteration on
-                               every unit that allows it (bf16, row-major
-                               apply, K >= 2), whatever its shape.  A
+                               where it saves time (default; bf16 NS, the
+                               row-major apply, K >= 2): those with S >= 128
+                               and L >= 1.25 S, and, with tile_policy 0, the
+                               others of a small plan too if all of them have
+                               128 to 512 rows and the launches saved by one
+                               kind of iteration outweigh the products' cost.
+                               With other coefficients than the paper's (2,
+                               -1.5, 0.5) only the first, and only if S is a
+                               multiple of 8 on every unit.  As printed
+                               elsewhere.  1 = as printed everywhere.  2 = the
+                               Gram-space iteration on every unit that allows
+                               it (bf16, row-major apply, K >= 2; with other
+                               coefficients S a multiple of 8 throughout),
+                               whatever its shape.  A
                                Gram-space unit keeps three more S x S
                                buffers. */
 } muonbp_options;
@@ -263,7 +271,9 @@ typedef struct {
                               packed, see pack_elements, and the pack's
                               tile list is longer)                            */
   int64_t device_bytes;    /* momentum + NS workspace + K-split sums of a
-                              context for these matrices (both plans)       */
+                              context for these matrices (both plans) made
+                              without a limit; a limit of this and room for
+                              the tables is enough                          */
   int64_t gram_units;      /* units that run the Gram-space iteration (see
                               muonbp_options.gram_iteration)                */
   int64_t pack_elements;   /* elements the pack copies into the NS workspace

@@ -75,8 +75,8 @@ struct GemmDesc {
 
 // Workgroup tile shapes of the NS GEMM (rows x columns of C per workgroup):
 // register-staged K loop (any dtype, any K) or LDS-DMA K loop (bf16, K a
-// multiple of 8 or rows padded with zeros to one; kGemmWaveK64: every wave of a workgroup runs a quarter of
-// the tile's K slices).
+// multiple of 8 or rows padded with zeros to one; kGemmWaveK64: every wave of
+// a workgroup runs a quarter of the tile's K slices).
 // kGemm128x128Split2 runs two K halves of each tile in one 8-wave
 // workgroup.  kGemmDma128x128 .. kGemmDma256x256 are kept as numbers only:
 // the planner turns them into the interleaved kernels of the same shapes.

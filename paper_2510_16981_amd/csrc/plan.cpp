@@ -58,14 +58,25 @@ bool place_problem(Problem* p, int64_t* cursor, int64_t align_elems, bool nn) {
 // A plan of both kinds of iteration has a Gram and an apply launch for every
 // iteration (its units as printed) on top of the Gram-space products: 23
 // launches for K = 5, against 17 where every unit runs the Gram-space
-// iteration (with the paper's quintic its U is 0.67 to 0.89 times as far from
-// 64 bits as printed, at ten sizes from 129 x 1000 to 999 x 1333 with gradients
-// of rank 4 to 128, L = S among them).  Down to L = S that is no more flops (20 S^3 either way), only
+// iteration.  Down to L = S that is no more flops (20 S^3 either way), only
 // more of them in the slower products, so where the launches saved are worth
-// more than that, the remaining units follow: none below kGramMinS, and none
-// above 512 rows, whose launches take several times their fixed cost.  A launch
+// more than that, the remaining units follow: none below kGramMinS (one such
+// unit leaves the whole plan as it is), and none above 512 rows.  A launch
 // of a small plan costs 4-5 us; rates as for kGramMinS, halved (launches of
 // few tiles).  The block step of one layer of width 512: 210 -> 188 us.
+//
+// 512 rows is where the measurements behind the model ended, not the break-even.
+// One S x S unit beside one S x 4 S / four beside three / sixteen beside twelve,
+// us, both kinds of iteration against Gram space only: S = 520 188 / 252 / 534
+// against 145 / 204 / 457, 768 230 / 387 / 854 against 172 / 297 / 771, 1024 314
+// / 506 / 1331 against 258 / 415 / 1379.
+//
+// Distance of U from 64 bits in Gram space over that as printed, of the units
+// that follow (L <= 1.17 S, S = 128 to 512, paper's quintic): 0.67 to 0.89 for
+// gradients of rank 4 to 128 with noise, whose distance is the largest (0.6 to
+// 1.8% as printed).  Full-rank Gaussian inputs, closer to 64 bits either way
+// (0.4 to 0.5%): 1.13 at S = 128, 1.09 at 192, 1.01 at 256, 0.99 at 320, 0.87 at
+// 512.  Orthonormal rows (0.3 to 0.4% as printed): 0.62 to 2.2, at most 0.66%.
 void unify_iteration(std::vector<Problem>* probs, int ns_steps) {
   double extra_us = 0;
   bool some = false, all = true;
@@ -670,7 +681,7 @@ std::string build_layout(const MatrixShape* mats, int32_t n_mats,
   // segment is one more term of its unit's scale (12.6 M elements in twice the
   // segments: k_scale 8.0 -> 10.7 us).
   bool aligned = true;
-  for (const MatrixShape& m : L.mats) aligned = aligned && m.cols % m.grid_cols == 0 && m.cols / m.grid_cols % 8 == 0;
+  for (const MatrixShape& m : L.mats) aligned = aligned && m.cols / m.grid_cols % 8 == 0;
   const int64_t least = (aligned ? 1 : 4) * kNumCUs;
   int64_t seg_target = kSegTarget;
   while (!lean && seg_target > 2048 && elems / seg_target < least) seg_target /= 2;
@@ -775,7 +786,10 @@ std::string build_layout(const MatrixShape* mats, int32_t n_mats,
     plan.nn_apply = apply_mode == 0 && gemm_reads_rows(plan.variant[kApply]);
     // Steeper polynomials than the paper's quintic lose precision in Gram
     // space (U of 129 x 1000 with a = 3.44 in two iterations: 0.87% from 64
-    // bits as printed, 2.7% in Gram space; with the quintic 0.95% and 0.73%):
+    // bits as printed, 2.7% in Gram space; with the quintic 0.95% and 0.73%, at
+    // odd sizes from 129 x 300 to 999 x 1333 0.59 to 0.88 of the distance as
+    // printed for gradients of rank 4 to 128 with noise, 0.81 to 0.98 for
+    // Gaussian inputs, 0.72 to 1.7 for orthonormal rows):
     // with other coefficients only the plans that have always run it do,
     // those whose units' smaller sides are all multiples of 8.
     bool chunks = true;

@@ -101,7 +101,8 @@ enum DescSlot {
 constexpr int kGramSegment = 3;
 
 // Gram-space iteration where it saves work (bf16 NS, the row-major apply,
-// K >= 2): on units with S >= kGramMinS and L >= 1.25 S.  A segment of n
+// K >= 2): on units with S >= kGramMinS and L >= 1.25 S, and in small plans on
+// the units beside them (unify_iteration in plan.cpp).  A segment of n
 // iterations costs one Gram (S x S x L), 4n - 3 symmetric S x S x S
 // products and one apply (S x L x S) against n of each of the Gram, the
 // polynomial and the apply; with segments of 3 the measured kernel rates
