@@ -158,9 +158,18 @@ hipError_t build_plan_tables(muonbp_ctx* c, int full) {
   if ((e = upload(c, &pd.pack, pk)) != hipSuccess) return e;
   if ((e = upload(c, &pd.pack_tiles, plan.pack_tiles)) != hipSuccess) return e;
   if ((e = upload(c, &pd.descs, descs)) != hipSuccess) return e;
-  pd.phase_tiles.assign(plan.phases.size(), nullptr);
-  for (size_t ph = 0; ph < plan.phases.size(); ++ph)
-    if ((e = upload(c, &pd.phase_tiles[ph], plan.phases[ph].tiles)) != hipSuccess) return e;
+  // The launches' tile lists back to back, in one allocation and copy.
+  std::vector<TileRef> tiles;
+  size_t n_tiles = 0;
+  for (const GemmPhase& ph : plan.phases) n_tiles += ph.tiles.size();
+  tiles.reserve(n_tiles);
+  for (const GemmPhase& ph : plan.phases) tiles.insert(tiles.end(), ph.tiles.begin(), ph.tiles.end());
+  TileRef* at = nullptr;
+  if ((e = upload(c, &at, tiles)) != hipSuccess) return e;
+  for (const GemmPhase& ph : plan.phases) {
+    pd.phase_tiles.push_back(at);
+    at += ph.tiles.size();
+  }
   if ((e = upload(c, &pd.upd, pd.upd_host)) != hipSuccess) return e;
   return hipSuccess;
 }
@@ -404,10 +413,15 @@ static muonbp_status create_ctx(const muonbp_matrix* mats, int32_t n_mats, int64
         hipSuccess)
       return bail(e, "split counters");
   }
-  if ((e = upload(c, &c->segs, c->lay.segs)) != hipSuccess) return bail(e, "segments");
-  if ((e = upload(c, &c->blocks, block_descs(c->lay))) != hipSuccess) return bail(e, "blocks");
-  for (int full = 0; full < 2; ++full)
-    if ((e = build_plan_tables(c, full)) != hipSuccess) return bail(e, "plan tables");
+  try {
+    if ((e = upload(c, &c->segs, c->lay.segs)) != hipSuccess) return bail(e, "segments");
+    if ((e = upload(c, &c->blocks, block_descs(c->lay))) != hipSuccess) return bail(e, "blocks");
+    for (int full = 0; full < 2; ++full)
+      if ((e = build_plan_tables(c, full)) != hipSuccess) return bail(e, "plan tables");
+  } catch (const std::bad_alloc&) {
+    free_ctx(c);
+    return MUONBP_E_NOMEM;
+  }
   if ((e = c->ptrs.init(shapes.size())) != hipSuccess) return bail(e, "pointer tables");
   if (o.check_finite) {
     if ((e = dev_alloc(c, &p, sizeof(int))) != hipSuccess) return bail(e, "finite flag");
