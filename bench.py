@@ -56,7 +56,9 @@ def log(msg):
 
 def gram_space_unit(S, L, K, mode, apply_nn):
     """Whether the library runs an S x L unit's K iterations in Gram space
-    (the planner's rule for bf16 NS; mode is the gram_iteration option)."""
+    (the planner's rule for bf16 NS with the default quintic, without its
+    exception for small plans, which no workload here is; mode is the
+    gram_iteration option)."""
     if mode == 1 or not apply_nn or K < 2:
         return False
     return mode == 2 or (S >= 128 and 4 * L >= 5 * S)
