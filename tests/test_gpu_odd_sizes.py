@@ -36,6 +36,7 @@ CASES = {
     "large tiles": dict(mats=[(1021, 1343, 1, 1)] * 6 + [(1343, 1021, 1, 1)] * 6, steps=1, rank=128),
     "NT apply": dict(mats=[(77, 203, 1, 1), (203, 77, 1, 1)], apply_mode=1, rank=64),
     "K split": dict(mats=[(301, 411, 1, 1), (411, 301, 1, 1)], k_split=3, rank=64),
+    "the planner's K split": dict(mats=[(129, 6149, 1, 1), (6151, 70, 1, 1), (200, 8201, 1, 1)], rank=64, steps=1),
     "nesterov, fp32 weights": dict(mats=[(301, 411, 1, 1), (411, 301, 1, 1)], nesterov=1, param="f32", rank=64),
 }
 
@@ -51,6 +52,8 @@ def test_odd_sizes(name):
     assert info.apply_nn == (0 if case.apply_mode else 1)  # only the DMA kernels read Z row-major
     if name == "large tiles":
         assert min(info.gemm_tile_rows) >= 128
+    if name == "the planner's K split":
+        assert info.gemm_split[0] == 3
     w = run_case(case).worst()
     announce(f"worst errors {w}")
     assert w["u"] <= TOL and w["u_unit"] <= TOL and w["u_tile"] <= TOL, w
